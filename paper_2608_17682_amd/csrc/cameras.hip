@@ -325,21 +325,13 @@ __global__ void __launch_bounds__(256) k_views_fwd_refill(ViewsArgs a) {
 
 // Backward work unit: a workgroup tile (the waves' tiles side by side, 2
 // wide), walked by the whole workgroup into one LDS gradient table that is
-// flushed to global memory before the next unit.  The persistent
-// one-lane-per-ray single-map adjoint is held to 128 VGPRs and a 528-entry
-// table, four workgroups of four waves per CU instead of three (it spills
-// 84 bytes per lane, a few of whose reloads fall inside the walk loop; the
-// extra wave still wins); the other forms keep the larger table.
-template <int LPR, int APP, bool PERSIST>
-struct BwdShape {
-  static constexpr bool quad = PERSIST && LPR == 1 && APP == 0;
-  static constexpr int waves = quad ? 4 : 1;
-  static constexpr int cap = quad ? kTableCapQuad : TableShape<APP>::cap;
-};
-
+// flushed to global memory before the next unit.  (Waves that took tiles one
+// by one, with no barrier and one flush at the end, were slower: the entries
+// of finished tiles then leave by takeover, inside the walk; 100k-site
+// forward + backward 1.38 -> 1.83 ms.)
 template <int LPR, int TEX, int APP, bool PERSIST>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(BwdShape<LPR, APP, PERSIST>::waves, 8)))
+    __attribute__((amdgpu_waves_per_eu(kBwdWaves, 8)))
     k_views_bwd(ViewsArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -351,17 +343,13 @@ __global__ void __launch_bounds__(256)
   const int unit_w = a.tile_w * wx;
   const int unit_h = a.tile_h * (nwaves / wx);
   const int RR = a.s.res * a.s.res;
-  constexpr int kCap = BwdShape<LPR, APP, PERSIST>::cap;
-  constexpr int kOb = TableShape<APP>::outbox;
-  __shared__ int s_keys[kCap];
-  __shared__ float s_vals[16 * kCap];
+  __shared__ __align__(16) int s_keys[kTableCap];
+  __shared__ __align__(16) float s_vals[16 * (kTableCap + 1)];
   __shared__ int s_unit;
-  __shared__ int s_okeys[4][kOb];
-  __shared__ float s_ovals[4][kStageStride * kOb];
-  GradTable<kCap> tab;
+  __shared__ __align__(16) float s_merge[4][kMergeFloats];
+  GradTable tab;
   tab.keys = s_keys;
   tab.vals = s_vals;
-  const Outbox ob{s_okeys[wave], s_ovals[wave], kOb};
   __shared__ unsigned long long s_stats[kWgStats];
   table_clear(tab);
   if constexpr (PERSIST) wg_stats_clear(s_stats);
@@ -408,7 +396,7 @@ __global__ void __launch_bounds__(256)
     // the whole wave walks its tile together (gradient records merge across
     // lanes); its counters go to the workgroup's LDS stats after each unit
     Counters cnt;
-    walk_backward<LPR, TEX, APP, kCap>(a.s, a.w, r, u, has, sub, lane, a.g, &tab, ob, cnt, false,
+    walk_backward<LPR, TEX, APP>(a.s, a.w, r, u, has, sub, lane, a.g, tab, s_merge[wave], cnt, false,
                                        ray_trace(a, has, tr.ray));
     if (a.stats) {
       if constexpr (PERSIST) {
@@ -642,6 +630,7 @@ static voro_status views_common(bool backward, const voro_scene* scene, const vo
   a.center_cell = centers;
   a.s = dev_scene(scene, ws);
   a.w = walk_params(params);
+  set_grad_layout(a.g, scene);
   // forward work units are wave tiles, backward units workgroup tiles
   const int nw = L.block / 64;
   const int wxu = nw >= 2 ? 2 : 1;
@@ -844,7 +833,6 @@ voro_status voro_render_views_bwd(const voro_scene* scene, void* ws, size_t ws_b
   a.g_rgb = g_rgb;
   a.g_T = g_T;
   a.g.texels = g_texels;
-  a.g.maps = scene && scene->tex_maps == 2 ? 2 : 1;
   a.stats = reinterpret_cast<unsigned long long*>(stats);
   if (scene && ws) a.g.cell = cell_grads(scene, ws);
   bool any_spp = false;

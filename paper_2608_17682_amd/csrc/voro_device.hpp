@@ -396,18 +396,67 @@ struct TexelT<VORO_TEX_F16> {
   }
 };
 
+// The four texels of a bilinear lookup as they are stored, so that they can be
+// loaded ahead of their use.  Half-precision texels of a row are neighbours of
+// 8 bytes each: one 16-byte load (8-byte aligned) holds both.
+template <int TEX>
+struct TexQuad {
+  using Row = uint32_t __attribute__((ext_vector_type(4), aligned(8)));
+  Row r0, r1;
+  __device__ __forceinline__ void load(const void* __restrict__ tex, size_t idx, int R) {
+    const uint2* p = reinterpret_cast<const uint2*>(tex) + idx;
+    r0 = *reinterpret_cast<const Row*>(p);
+    r1 = *reinterpret_cast<const Row*>(p + R);
+  }
+  __device__ __forceinline__ void settle() { asm volatile("" : "+v"(r0), "+v"(r1)); }
+  __device__ __forceinline__ void get(float4& a, float4& b, float4& e, float4& f) const {
+    const uint2 h[4] = {{r0.x, r0.y}, {r0.z, r0.w}, {r1.x, r1.y}, {r1.z, r1.w}};
+    a = TexelT<TEX>::load(&h[0], 0);
+    b = TexelT<TEX>::load(&h[1], 0);
+    e = TexelT<TEX>::load(&h[2], 0);
+    f = TexelT<TEX>::load(&h[3], 0);
+  }
+};
+
+template <>
+struct TexQuad<VORO_TEX_F32> {
+  float4 t[4];
+  __device__ __forceinline__ void load(const void* __restrict__ tex, size_t idx, int R) {
+    const float4* p = reinterpret_cast<const float4*>(tex) + idx;
+    t[0] = p[0];
+    t[1] = p[1];
+    t[2] = p[R];
+    t[3] = p[R + 1];
+  }
+  __device__ __forceinline__ void settle() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(t[i].x), "+v"(t[i].y), "+v"(t[i].z));
+  }
+  __device__ __forceinline__ void get(float4& a, float4& b, float4& e, float4& f) const {
+    a = t[0];
+    b = t[1];
+    e = t[2];
+    f = t[3];
+  }
+};
+
+template <int TEX>
+__device__ __forceinline__ void quad_rgb(const TexQuad<TEX>& t, const Taps& tp, float& r, float& g,
+                                         float& b) {
+  float4 a, c, e, f;
+  t.get(a, c, e, f);
+  r = fmaf(tp.w11, f.x, fmaf(tp.w10, e.x, fmaf(tp.w01, c.x, tp.w00 * a.x)));
+  g = fmaf(tp.w11, f.y, fmaf(tp.w10, e.y, fmaf(tp.w01, c.y, tp.w00 * a.y)));
+  b = fmaf(tp.w11, f.z, fmaf(tp.w10, e.z, fmaf(tp.w01, c.z, tp.w00 * a.z)));
+}
+
 // Bilinear colour of cell i at the ray's taps.
 template <int TEX>
 __device__ __forceinline__ void texel_rgb(const void* __restrict__ tex, int i, int R, const Taps& tp,
                                           float& r, float& g, float& b) {
-  const size_t base = (size_t)i * (size_t)(R * R) + (size_t)tp.base;
-  const float4 a = TexelT<TEX>::load(tex, base);
-  const float4 c = TexelT<TEX>::load(tex, base + 1);
-  const float4 e = TexelT<TEX>::load(tex, base + R);
-  const float4 f = TexelT<TEX>::load(tex, base + R + 1);
-  r = fmaf(tp.w11, f.x, fmaf(tp.w10, e.x, fmaf(tp.w01, c.x, tp.w00 * a.x)));
-  g = fmaf(tp.w11, f.y, fmaf(tp.w10, e.y, fmaf(tp.w01, c.y, tp.w00 * a.y)));
-  b = fmaf(tp.w11, f.z, fmaf(tp.w10, e.z, fmaf(tp.w01, c.z, tp.w00 * a.z)));
+  TexQuad<TEX> t;
+  t.load(tex, (size_t)i * (size_t)(R * R) + (size_t)tp.base, R);
+  quad_rgb<TEX>(t, tp, r, g, b);
 }
 
 // ------------------------------------------------ full appearance model
@@ -432,11 +481,9 @@ __device__ __forceinline__ void full_logits(const void* __restrict__ tex, int i,
                                             const Taps& ts, const Taps& tv, float& lr, float& lg,
                                             float& lb, float4& a, float4& b, float4& e,
                                             float4& f) {
-  const size_t base = (size_t)(2 * i) * (size_t)(R * R) + (size_t)ts.base;
-  a = TexelT<TEX>::load(tex, base);
-  b = TexelT<TEX>::load(tex, base + 1);
-  e = TexelT<TEX>::load(tex, base + R);
-  f = TexelT<TEX>::load(tex, base + R + 1);
+  TexQuad<TEX> t;
+  t.load(tex, (size_t)(2 * i) * (size_t)(R * R) + (size_t)ts.base, R);
+  t.get(a, b, e, f);
   float vr, vg, vb;
   texel_rgb<TEX>(tex, 2 * i + 1, R, tv, vr, vg, vb);
   lr = fmaf(ts.w11, f.x, fmaf(ts.w10, e.x, fmaf(ts.w01, b.x, ts.w00 * a.x))) + vr;

@@ -219,19 +219,9 @@ __global__ void __launch_bounds__(256)
   if (a.stats) flush_counters(cnt, sub == 0, lane, a.stats);
 }
 
-// The one-lane-per-ray single-map form runs at four waves per SIMD with the
-// 528-entry table (as the persistent multi-view adjoint); the others keep
-// the larger table at three.
-template <int LPR, int APP>
-struct RenderBwdShape {
-  static constexpr bool quad = LPR == 1 && APP == 0;
-  static constexpr int waves = quad ? 4 : 1;
-  static constexpr int cap = quad ? kTableCapQuad : TableShape<APP>::cap;
-};
-
 template <int LPR, int TEX, int APP>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(RenderBwdShape<LPR, APP>::waves, 8)))
+    __attribute__((amdgpu_waves_per_eu(kBwdWaves, 8)))
     k_render_bwd(RayArgs a) {
   const int nwaves = blockDim.x >> 6;
   const int wave = threadIdx.x >> 6;
@@ -267,21 +257,17 @@ __global__ void __launch_bounds__(256)
       u.gD = a.g_dist[ray];
     }
   }
-  constexpr int kCap = RenderBwdShape<LPR, APP>::cap;
-  constexpr int kOb = TableShape<APP>::outbox;
-  __shared__ int s_keys[kCap];
-  __shared__ float s_vals[16 * kCap];
-  __shared__ int s_okeys[4][kOb];
-  __shared__ float s_ovals[4][kStageStride * kOb];
-  GradTable<kCap> tab;
+  __shared__ __align__(16) int s_keys[kTableCap];
+  __shared__ __align__(16) float s_vals[16 * (kTableCap + 1)];
+  __shared__ __align__(16) float s_merge[4][kMergeFloats];
+  GradTable tab;
   tab.keys = s_keys;
   tab.vals = s_vals;
-  const Outbox ob{s_okeys[wave], s_ovals[wave], kOb};
   table_clear(tab);
   __syncthreads();
   // all lanes take part: the gradient records are merged across the wave,
   // then across the workgroup in the LDS table
-  walk_backward<LPR, TEX, APP, kCap>(a.s, a.w, r, u, ray >= 0, sub, lane, a.g, &tab, ob, cnt,
+  walk_backward<LPR, TEX, APP>(a.s, a.w, r, u, ray >= 0, sub, lane, a.g, tab, s_merge[wave], cnt,
                                a.g_dist != nullptr, ray_exits(a, ray));
   __syncthreads();
   table_flush(tab, a.g, a.s.res * a.s.res, a.s.res);
@@ -383,6 +369,7 @@ static voro_status ray_launch(bool backward, const voro_scene* scene, const void
   const Launch L = resolve_launch(params);
   a.s = dev_scene(scene, ws);
   a.w = walk_params(params);
+  set_grad_layout(a.g, scene);
   a.o = o;
   a.d = d;
   a.tmax = tmax;
@@ -491,7 +478,6 @@ voro_status voro_render_bwd(const voro_scene* scene, void* ws, size_t ws_bytes,
   a.dist_in = dist;
   a.g_dist = g_dist;
   a.g.texels = g_texels;
-  a.g.maps = scene && scene->tex_maps == 2 ? 2 : 1;
   a.stats = reinterpret_cast<unsigned long long*>(stats);
   if (scene && ws) a.g.cell = cell_grads(scene, ws);
   voro_status st =

@@ -55,7 +55,21 @@ struct Grads {
   float4* cell;    // [N] workspace accumulator: (dp.x, dp.y, dp.z, dsigma)
   float* texels;   // [N,R,R,4], or [N,2,R,R,4] for the full appearance model
   int maps;        // texture maps per cell (1 or 2)
+  unsigned rr_mul; // key / R^2 = umulhi(key, rr_mul) >> rr_shift (set_grad_layout)
+  int rr_shift;
 };
+
+// Exact quotients by RR = R^2 (4 <= RR <= 256) of any key in [0, 2^31): with
+// 2^L >= RR and m = ceil(2^(31+L) / RR), m RR - 2^(31+L) < RR <= 2^L, so the
+// error key (m RR - 2^(31+L)) / (RR 2^(31+L)) stays below 1 / RR.
+inline void set_grad_layout(Grads& g, const voro_scene* s) {
+  g.maps = s->tex_maps == 2 ? 2 : 1;
+  const unsigned RR = (unsigned)(s->tex_res * s->tex_res);
+  int L = 0;
+  while ((1u << L) < RR) ++L;
+  g.rr_mul = (unsigned)(((1ull << (31 + L)) + RR - 1) / RR);
+  g.rr_shift = L - 1;
+}
 
 struct Counters {
   uint32_t rays = 0, steps = 0, deg = 0, maxsteps = 0, nan = 0, bad = 0, redecide = 0,
@@ -459,12 +473,10 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
 // segment and from its two faces on the ray, i.e. from three consecutive
 // steps.  Each lane keeps a sliding window (previous cell, current cell, next
 // cell) and emits a cell's finished record - dsigma, dp (3), 12 texel terms -
-// once, one step after leaving it.  Before the atomics, the records of the
-// whole wave are merged on a butterfly: partner lanes (lane ^ m) holding the
-// same key (cell, texel quad) add up and one of them retires, so coherent
-// rays crossing the same cell issue one set of atomics instead of one per
-// lane.  Faces whose far cell has already been emitted (only after zero-length
-// segments) go straight to the atomics.
+// once, one step after leaving it.  The records of a wave that share a key
+// (cell, texel quad) are summed before they go to the workgroup's table and
+// from there to global memory.  Faces whose far cell has already been emitted
+// (only after zero-length segments) go straight to the atomics.
 
 __device__ __forceinline__ void atomic_site(const Grads& g, int cell, float x, float y, float z) {
   float* p = reinterpret_cast<float*>(g.cell + cell);
@@ -477,7 +489,7 @@ __device__ __forceinline__ void atomic_site(const Grads& g, int cell, float x, f
 // c (0..15): 0 dsigma, 1-3 dp, 4-15 the texel terms of taps (r0,c0),
 // (r0,c0+1), (r0+1,c0), (r0+1,c0+1) x RGB of that map.
 __device__ __forceinline__ float* record_addr(const Grads& g, int key, int c, int RR, int R) {
-  const int cm = key / RR;
+  const int cm = (int)(__umulhi((unsigned)key, g.rr_mul) >> g.rr_shift);
   const int base = key - cm * RR;
   const int cell = g.maps == 2 ? (cm >> 1) : cm;
   if (c < 4) return reinterpret_cast<float*>(g.cell + cell) + (c == 0 ? 3 : c - 1);
@@ -487,251 +499,229 @@ __device__ __forceinline__ float* record_addr(const Grads& g, int key, int c, in
          ch;
 }
 
-// Per-wave LDS staging of records bound for global memory: 16 lanes then
-// write one record's 16 terms with one instruction, so a record costs about
-// four cache-line requests at the memory-side atomic units instead of
-// sixteen.  The area holds `cap` records; more senders go in turns.  With
-// the full appearance model the same area also stages the survivors bound
-// for the workgroup table (see emit_records), laid out [record][kStageStride],
-// and then holds a whole wave (64 records).
-constexpr int kStageStride = 17;  // odd: both access patterns spread over the banks
-struct Outbox {
-  int* keys;    // [cap]
-  float* vals;  // [kStageStride * cap]
-  int cap;
-};
+// Workgroup gradient table in LDS: a four-way cache of 16 FP32 sums per record
+// key (cell * R^2 + texel quad).  A wave adds to an entry under the entry's
+// lock (the sign bit of its key word); a key whose four ways all hold other
+// keys takes one of them over, and the sums it held go to global memory.  The
+// rest reach global memory when the workgroup flushes.
+//
+// What bounds the adjoint: device float atomics leave a CU at most 64 bytes at
+// a time and the chip at 20 G requests/s, wherever the line is held, and LDS
+// float atomics take 3 cycles per active lane (193 per full wave; a read and a
+// write together 5.6).  So records are summed across the wave first, exactly
+// (emit_records), the sums are added by plain reads and writes, and entries
+// that later rays cannot reach any more make room for new ones.  4M sites, 8
+// views: device requests 817 M -> 250 M, LDS busy 0.78 -> 0.2, adjoint 51.9 ->
+// 29.2 ms; 100k sites, 800x800: 1.17 -> 0.72 ms (two maps: 2.40 -> 1.50 ms).
+// Taking over a fixed way per key instead of one that moves on with the steps
+// left finished cells in place: 32.0 ms at 4M sites.  Locking with a loop over
+// single slots instead of one 16-byte read of a set cost 240 us of the 100k
+// adjoint; LDS float atomics on the merged sums instead of the lock, 100 us.
+// 512 entries are what leaves room for three workgroups per CU beside the
+// merge areas (four waves per SIMD instead of three spill inside the walk:
+// 63.6 against 62.0 ms per 4M-site step).
+constexpr int kBwdWaves = 3;      // waves per SIMD of every adjoint kernel
+constexpr int kTableCap = 512;
+constexpr int kTableTries = 16;   // rounds before a contended sum goes to global memory
+constexpr int kTableLock = (int)0x80000000;
 
-// Every lane of the wave must call this; `send` lanes hand over (key, v).
-__device__ __forceinline__ void outbox_send(const Outbox& ob, bool send, int key, const float* v,
-                                            int lane, const Grads& g, int RR, int R) {
-  const unsigned long long m = __ballot(send);
-  if (m == 0ull) return;
-  const int pos = __popcll(m & ((1ull << lane) - 1ull));
-  const int total = __popcll(m);
-  const int cap = ob.cap;
-  for (int b0 = 0; b0 < total; b0 += cap) {
-    if (send && pos >= b0 && pos < b0 + cap) {
-      ob.keys[pos - b0] = key;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) ob.vals[c * cap + pos - b0] = v[c];
-    }
-    __builtin_amdgcn_wave_barrier();
-    const int n = min(cap, total - b0);
-    for (int b = 0; b < n; b += 4) {
-      const int r = b + (lane >> 4);
-      const int c = lane & 15;
-      if (r < n) {
-        const float x = ob.vals[c * cap + r];
-        if (x != 0.0f) atomicAdd(record_addr(g, ob.keys[r], c, RR, R), x);
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// Workgroup gradient table in LDS: open addressing on the record key
-// (cell * R^2 + texel quad), 16 FP32 sums per entry stored term-major so
-// that lanes adding to different entries hit different banks.  Records are
-// added with LDS float atomics while the workgroup walks its rays; every
-// entry then reaches global memory once, when the workgroup flushes.  A
-// record that finds no slot within kTableProbes goes straight to global
-// memory.  Capacity: as many entries as leave room for three workgroups
-// of four waves per CU (a larger table that costs a workgroup, or more
-// probes, measured slower; so did a smaller table with four workgroups).
-constexpr int kTableProbes = 8;
-constexpr int kTableCapSingle = 704;  // one texture map: 16-record outboxes beside it
-// the persistent one-lane-per-ray single-map adjoint runs four workgroups of
-// four waves per CU: 528 entries is the most that leaves LDS for four
-constexpr int kTableCapQuad = 528;
-constexpr int kTableCapFull = 512;    // two maps: the outboxes also stage a whole wave
-constexpr int kOutboxSingle = 16;
-constexpr int kOutboxFull = 64;
-
-template <int APP>
-struct TableShape {
-  static constexpr int cap = APP == 1 ? kTableCapFull : kTableCapSingle;
-  static constexpr int outbox = APP == 1 ? kOutboxFull : kOutboxSingle;
-};
-
-// The capacity is a compile-time constant: a run-time one made the adjoint
-// spill registers to scratch memory.
-template <int CAP>
 struct GradTable {
-  static constexpr int cap = CAP;
-  int* keys;    // [cap], -1 = empty
-  float* vals;  // [16][cap]
+  int* keys;    // [kTableCap], -1 = empty, key | kTableLock = held by a wave
+  float* vals;  // [kTableCap + 1][16]; the last is written for keys without an entry
 };
-
-// home slot of a key: multiplicative hash scaled to [0, cap)
-template <int CAP>
-__device__ __forceinline__ int table_home(const GradTable<CAP>& t, int key) {
-  const unsigned h = (unsigned)key * 2654435761u;
-  return (int)(((unsigned long long)h * (unsigned)CAP) >> 32);
-}
 
 // all threads of the workgroup; needs a barrier before the table is used
-template <int CAP>
-__device__ __forceinline__ void table_clear(const GradTable<CAP>& t) {
-  for (int i = threadIdx.x; i < t.cap; i += blockDim.x) {
-    t.keys[i] = -1;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) t.vals[c * t.cap + i] = 0.0f;
-  }
+__device__ __forceinline__ void table_clear(const GradTable& t) {
+  for (int i = threadIdx.x; i < kTableCap; i += blockDim.x) t.keys[i] = -1;
+  for (int i = threadIdx.x; i < kTableCap * 16; i += blockDim.x) t.vals[i] = 0.0f;
 }
 
-// the record's table slot (claimed if new), or -1 when kTableProbes probes
-// (linear, wrapping) find neither the key nor an empty slot
-template <int CAP>
-__device__ __forceinline__ int table_slot(const GradTable<CAP>& t, int key) {
-  int slot = table_home(t, key);
-  for (int p = 0; p < kTableProbes; ++p) {
-    int k = __hip_atomic_load(&t.keys[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (k == -1) k = atomicCAS(&t.keys[slot], -1, key);
-    if (k == -1 || k == key) return slot;
-    slot = slot + 1 == t.cap ? 0 : slot + 1;
-  }
-  return -1;
-}
-
-// C0: the first term that may be nonzero (texel-only records start at 4)
-template <int C0, int CAP>
-__device__ __forceinline__ bool table_add(const GradTable<CAP>& t, int key, const float* v) {
-  const int slot = table_slot(t, key);
-  if (slot < 0) return false;
+// Lock the entry of `key`, taking one over if need be: its slot, or -1 when
+// another lane or wave holds the entry that would be taken (never waits).
+// old: the key whose sums the entry holds, -1 if none.  age moves the way
+// that is taken over.
+__device__ __forceinline__ int table_lock(const GradTable& t, int key, unsigned age, int& old) {
+  const unsigned h = (unsigned)key * 2654435761u;
+  const int set = (int)(((unsigned long long)h * (unsigned)(kTableCap / 4)) >> 32);
+  using i32x4 = int __attribute__((ext_vector_type(4)));
+  const i32x4 k = *reinterpret_cast<const volatile i32x4*>(t.keys + 4 * set);
+  const int turn = (h + age) & 3;   // the way taken over when all four are full
+  int way = turn;
+  int e = turn == 0 ? k.x : turn == 1 ? k.y : turn == 2 ? k.z : k.w;
 #pragma unroll
-  for (int c = C0; c < 16; ++c)
-    if (v[c] != 0.0f) atomicAdd(&t.vals[c * t.cap + slot], v[c]);
-  return true;
+  for (int w = 3; w >= 0; --w) {
+    way = k[w] == -1 ? w : way;
+    e = k[w] == -1 ? -1 : e;
+  }
+#pragma unroll
+  for (int w = 3; w >= 0; --w) {
+    const bool hit = (k[w] & ~kTableLock) == key;
+    way = hit ? w : way;
+    e = hit ? k[w] : e;
+  }
+  old = e;
+  if (e < -1) return -1;  // held
+  const int slot = 4 * set + way;
+  return atomicCAS(&t.keys[slot], e, key | kTableLock) == e ? slot : -1;
 }
 
 // all threads of the workgroup, after a barrier: every entry to global
 // memory once (16 consecutive threads per entry, one term each), and the
 // table left empty (a barrier must follow)
-template <int CAP>
-__device__ __forceinline__ void table_flush(const GradTable<CAP>& t, const Grads& g, int RR,
+__device__ __forceinline__ void table_flush(const GradTable& t, const Grads& g, int RR,
                                             int R) {
-  for (int i = threadIdx.x; i < t.cap * 16; i += blockDim.x) {
-    const int slot = i >> 4;
-    const int c = i & 15;
-    const int key = t.keys[slot];
+  for (int i = threadIdx.x; i < kTableCap * 16; i += blockDim.x) {
+    const int key = t.keys[i >> 4];
     if (key < 0) continue;
-    const float x = t.vals[c * t.cap + slot];
-    t.vals[c * t.cap + slot] = 0.0f;
-    if (x != 0.0f) atomicAdd(record_addr(g, key, c, RR, R), x);
+    const float x = t.vals[i];
+    t.vals[i] = 0.0f;
+    if (x != 0.0f) atomicAdd(record_addr(g, key, i & 15, RR, R), x);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < t.cap; i += blockDim.x) t.keys[i] = -1;
+  for (int i = threadIdx.x; i < kTableCap; i += blockDim.x) t.keys[i] = -1;
 }
 
-// Value of lane ^ M, exchanged without the LDS: DPP quad permutations
-// (xor 1, 2), a half-row mirror followed by a quad reversal (xor 7 then
-// xor 3, i.e. xor 4), DPP row rotation by 8 (xor 8 within a row of 16) and
-// the row/half swaps of permlane16/32 (xor 16, 32; element 0 holds the even
-// row / lower half, element 1 the other).  Every lane of the wave must take
-// part.  (A ds_swizzle for xor 4 goes through the LDS, which the gradient
-// table keeps busy: the two DPP moves made the adjoint 2-6% faster.)
-template <int M>
-__device__ __forceinline__ int xor_lane(int x, int lane) {
-  if constexpr (M == 1) {
-    return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
-  } else if constexpr (M == 2) {
-    return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
-  } else if constexpr (M == 4) {
-    const int h = __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false);  // row_half_mirror
-    return __builtin_amdgcn_update_dpp(0, h, 0x1B, 0xF, 0xF, false);  // quad_perm [3,2,1,0]
-  } else if constexpr (M == 8) {
-    return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false); // row_ror:8
-  } else if constexpr (M == 16) {
-    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    return (lane & 16) ? (int)p[0] : (int)p[1];
-  } else {
-    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    return (lane & 32) ? (int)p[0] : (int)p[1];
-  }
+// Orders a wave's own LDS accesses for the compiler (the hardware keeps them in
+// order).
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// One butterfly level: partners holding the same key add up and the upper
-// one retires (terms below C0 are zero by construction and not exchanged).
-// Every lane of the wave must call this.
-template <int M, int C0>
-__device__ __forceinline__ void merge_level(int& key, float (&v)[16], int lane) {
-  const int pk = xor_lane<M>(key, lane);
-  const bool match = key >= 0 && pk == key;
-  if (!__any(match)) return;
-  // each partner term is added as it arrives (two registers in flight, not
-  // sixteen)
-  const bool add = match && (lane & M) == 0;
-#pragma unroll
-  for (int i = C0; i < 16; ++i) {
-    const float p = __int_as_float(xor_lane<M>(__float_as_int(v[i]), lane));
-    v[i] = add ? v[i] + p : v[i];
-  }
-  if (match && (lane & M) != 0) key = -1;
-}
+// One wave's LDS area for merging its records: row c < 16 holds term c of
+// every lane, row 16 the lanes' ranks and other words of the merge.
+constexpr int kMergeStride = 68;  // 16-byte rows that start four banks apart
+constexpr int kMergeFloats = 17 * kMergeStride;
 
-// Merge equal-key records of butterfly partners across the wave (lane ^ m
-// for m = LPR .. 32), then add the survivors to the workgroup table (or, with
-// no table, to global memory).  Every lane of the wave must call this (key <
-// 0: no record).
-// The texel term of tap t and channel ch is tap weight t x m_ch.  C0 = 4
-// marks a texel-only record (ds and dp are zero and skipped).
-// SPREAD: each survivor only claims its table slot and stages its terms;
-// then 16 lanes per record add them, so one LDS add instruction covers four
-// records instead of one term of every survivor.  It needs a few more
-// registers: a win for the full appearance model, whose two records per step
-// already hold it at two waves per SIMD (3.58 -> 3.02 ms per frame), a loss
-// for the single map, which it would push from three waves to two.
-template <int LPR, int C0, bool SPREAD, int CAP>
+// Merge the wave's records by key and add the sums to the workgroup table.
+// Every lane of the wave must call this (key < 0: no record).  The texel term
+// of tap t and channel ch is tap weight t x m_ch.  C0 = 4 marks a texel-only
+// record.  settle() runs before the first global atomic.
+//
+// The wave's keys are ranked; then, 16 at a time, a 16 x 64 matrix of
+// zeros and ones (rank of lane k is m) times the 64 x 16 matrix of the lanes'
+// terms gives each key's 16 sums in FP32 on the matrix cores, laid out so that
+// 16 lanes hold one key's terms: the table's and the atomics' order.  A wave
+// of 64 rays stands in about 6 distinct (cell, quad)s a step on the 100k-site
+// scene and 16 on the 4M-site one; a butterfly over lane ^ m, which it
+// replaces, left 20 and 38 records and took three times the VALU work.
+template <int C0, class F>
 __device__ __forceinline__ void emit_records(int key, float ds, float px, float py, float pz,
                                              const Taps& tp, float mr, float mg, float mb, int lane,
-                                             int RR, int R, const Grads& g,
-                                             const GradTable<CAP>* tab,
-                                             const Outbox& ob) {
-  float v[16];
-  v[0] = ds;
-  v[1] = px;
-  v[2] = py;
-  v[3] = pz;
+                                             int RR, int R, const Grads& g, const GradTable& tab,
+                                             float* area, unsigned age, F&& settle) {
+  if (!__any(key >= 0)) return;
+  float* rank_row = area + 16 * kMergeStride;
+  int* word = reinterpret_cast<int*>(rank_row);
+  area[0 * kMergeStride + lane] = ds;
+  area[1 * kMergeStride + lane] = px;
+  area[2 * kMergeStride + lane] = py;
+  area[3 * kMergeStride + lane] = pz;
   const float q[4] = {tp.w00, tp.w01, tp.w10, tp.w11};
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    v[4 + 3 * t] = q[t] * mr;
-    v[5 + 3 * t] = q[t] * mg;
-    v[6 + 3 * t] = q[t] * mb;
+    area[(4 + 3 * t) * kMergeStride + lane] = q[t] * mr;
+    area[(5 + 3 * t) * kMergeStride + lane] = q[t] * mg;
+    area[(6 + 3 * t) * kMergeStride + lane] = q[t] * mb;
   }
-  if constexpr (LPR <= 1) merge_level<1, C0>(key, v, lane);
-  if constexpr (LPR <= 2) merge_level<2, C0>(key, v, lane);
-  if constexpr (LPR <= 4) merge_level<4, C0>(key, v, lane);
-  if constexpr (LPR <= 8) merge_level<8, C0>(key, v, lane);
-  if constexpr (LPR <= 16) merge_level<16, C0>(key, v, lane);
-  merge_level<32, C0>(key, v, lane);
-  if constexpr (SPREAD) {
-    int slot = -1;
-    if (key >= 0 && tab) slot = table_slot(*tab, key);
-    const unsigned long long m = __ballot(slot >= 0);
-    if (m) {
-      const int pos = __popcll(m & ((1ull << lane) - 1ull));
-      if (slot >= 0) {
-        ob.keys[pos] = slot;
+  const int n = lane & 15;
+  const int grp = lane >> 4;
+  // Rank the distinct keys: each lane writes its number to a bucket chosen by
+  // its key and reads back whose stayed; lanes whose key is that lane's have
+  // their leader, the others go on with another hash.  Every round settles at
+  // least one key.
+  int rank = -1, total = 0;
+  bool leads = false;
+  {
+    unsigned char* bucket = reinterpret_cast<unsigned char*>(word);
+    bool open = key >= 0;
+    unsigned mul = 2654435761u;
+    do {
+      const unsigned h = ((unsigned)key * mul) >> 24;
+      int lead = lane;
+      if (open) bucket[h] = (unsigned char)lane;
+      lds_order();
+      if (open) lead = bucket[h];
+      lds_order();
+      const bool won = open && __builtin_amdgcn_ds_bpermute(4 * lead, key) == key;
+      const bool own = won && lead == lane;
+      const unsigned long long m = __ballot(own);
+      const int r = total + __popcll(m & ((1ull << lane) - 1ull));
+      const int lr = __builtin_amdgcn_ds_bpermute(4 * lead, r);
+      rank = won ? lr : rank;
+      leads = leads || own;
+      total += __popcll(m);
+      open = open && !won;
+      mul = mul * 0x9E3779B1u + 0x7F4A7C15u | 1u;
+    } while (__any(open));
+  }
+  for (int base = 0; base < total; base += 16) {
+    using f32x4 = float __attribute__((ext_vector_type(4)));
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    word[lane] = rank - base;
+    lds_order();
 #pragma unroll
-        for (int c = C0; c < 16; ++c) ob.vals[pos * kStageStride + c] = v[c];
+    for (int j = 0; j < 4; ++j) {
+      const f32x4 b = *reinterpret_cast<const f32x4*>(area + n * kMergeStride + 16 * grp + 4 * j);
+      const int4 rk = *reinterpret_cast<const int4*>(word + 16 * grp + 4 * j);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rk.x == n ? 1.0f : 0.0f, b.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rk.y == n ? 1.0f : 0.0f, b.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rk.z == n ? 1.0f : 0.0f, b.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rk.w == n ? 1.0f : 0.0f, b.w, acc, 0, 0, 0);
+    }
+    lds_order();
+    const bool now = rank >= base && rank < base + 16;
+    if (leads && now) word[rank - base] = key;
+    lds_order();
+    const int cnt = min(16, total - base);
+    int mine = lane < cnt ? word[lane] : -1;
+    if (base == 0) settle();
+    const float big = fabsf(acc.x) + fabsf(acc.y) + fabsf(acc.z) + fabsf(acc.w);
+    if (__any(!(big < kInf))) {
+      // an infinity or NaN would reach every sum (0 x inf): each record of
+      // this pass goes to global memory by itself
+      for (int c = C0; c < 16; ++c) {
+        const float x = area[c * kMergeStride + lane];
+        if (now && x != 0.0f) atomicAdd(record_addr(g, key, c, RR, R), x);
       }
-      __builtin_amdgcn_wave_barrier();
-      const int n = __popcll(m);
-      for (int b = 0; b < n; b += 4) {
-        const int r = b + (lane >> 4);
-        const int c = lane & 15;
-        if (r < n && c >= C0) {
-          const float x = ob.vals[r * kStageStride + c];
-          if (x != 0.0f) atomicAdd(&tab->vals[c * tab->cap + ob.keys[r]], x);
+      continue;
+    }
+    const float a4[4] = {acc.x, acc.y, acc.z, acc.w};
+    for (int it = 0; __any(mine >= 0); ++it) {
+      // the last round sends what found no entry to global memory
+      int slot = -1, old = -1;
+      const bool last = it >= kTableTries;
+      if (mine >= 0 && !last) slot = table_lock(tab, mine, age, old);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      // what becomes of the sums the entry holds: kept (-2), none (-1), or
+      // another key's, to be sent
+      if (slot >= 0) old = old == mine ? -2 : old;
+      if (lane < 16) {
+        word[lane] = slot >= 0 ? slot : kTableCap;
+        word[16 + lane] = slot >= 0 ? old : last ? mine : -1;
+      }
+      lds_order();
+      const int4 sl = *reinterpret_cast<const int4*>(word + 4 * grp);
+      const int4 ky = *reinterpret_cast<const int4*>(word + 16 + 4 * grp);
+      const int s4[4] = {sl.x, sl.y, sl.z, sl.w};
+      const int k4[4] = {ky.x, ky.y, ky.z, ky.w};
+      float x4[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x4[i] = tab.vals[16 * s4[i] + n];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tab.vals[16 * s4[i] + n] = a4[i] + (k4[i] == -2 ? x4[i] : 0.0f);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      if (slot >= 0)
+        __hip_atomic_store(&tab.keys[slot], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (__any(old >= 0 || (last && mine >= 0))) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float x = last ? a4[i] : x4[i];
+          if (k4[i] >= 0 && x != 0.0f) atomicAdd(record_addr(g, k4[i], n, RR, R), x);
         }
       }
-      __builtin_amdgcn_wave_barrier();
+      if (slot >= 0 || last) mine = -1;
     }
-    outbox_send(ob, key >= 0 && slot < 0, key, v, lane, g, RR, R);
-  } else {
-    const bool over = key >= 0 && !(tab && table_add<C0, CAP>(*tab, key, v));
-    outbox_send(ob, over, key, v, lane, g, RR, R);
   }
 }
 
@@ -752,11 +742,11 @@ __device__ __forceinline__ void emit_records(int key, float ds, float px, float 
 // and sum_j G_j w_j = 2 L_dist, so the suffix follows from the saved loss;
 // the interval ends move with their crossings through
 // dL_dist/dt = (dL/dsbar / 2 -+ dL/dds) s'(t), s'(t) = 1/(1+t)^2.
-template <int LPR, int TEX, int APP, int CAP = TableShape<APP>::cap>
+template <int LPR, int TEX, int APP>
 __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParams& w, const RayIn& r,
                                               const Upstream& u, bool has_ray, int sub, int lane,
-                                              const Grads& g, const GradTable<CAP>* tab,
-                                              const Outbox& ob, Counters& cnt,
+                                              const Grads& g, const GradTable& tab,
+                                              float* area, Counters& cnt,
                                               bool dist_on = false, const ExitTrace& xt = {}) {
   const int R = s.res;
   const int RR = R * R;
@@ -779,6 +769,22 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
   constexpr bool kCarry = APP == 0;
   float4 here = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (kCarry && active) here = s.cells[2 * (size_t)cur];
+  // Loads run ahead of their use (single map): the texels of the cell entered
+  // next, the stored exits of the next two steps and the far site of the next
+  // one's exit face are all under way while a step's records are merged.  They
+  // fill the registers that three waves per SIMD leave (168; spilled to 128 for
+  // a fourth wave they cost 40%, without them four waves were 4% slower).
+  TexQuad<TEX> tx;
+  int2 e0 = make_int2(0, -1), e1 = make_int2(0, -1);
+  float4 ahead = here;
+  if (kCarry && active) {
+    tx.load(s.texels, (size_t)cur * (size_t)RR + (size_t)tp.base, R);
+    if (xt.p) {
+      e0 = xt.p[0];
+      if (xt.cap > 1) e1 = xt.p[xt.stride];
+      if (e0.y >= 0 && e0.y < s.n) ahead = s.cells[2 * (size_t)e0.y];
+    }
+  }
 
   int k = 0;
   // previous cell's record (emitted one step late): its texel multipliers
@@ -793,6 +799,15 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
   // the entry face: cells (fa, fb) and dt/dp_fa, dt/dp_fb
   int fa = -1, fb = -1;
   float uax = 0.0f, uay = 0.0f, uaz = 0.0f, ubx = 0.0f, uby = 0.0f, ubz = 0.0f;
+  // wait for the loads under way before the records' global atomics follow
+  // them (their counter is shared and in order)
+  auto settle = [&] {
+    if constexpr (kCarry) {
+      asm volatile("" : "+v"(e1.x), "+v"(e1.y), "+v"(ahead.x), "+v"(ahead.y), "+v"(ahead.z), "+v"(ahead.w));
+      tx.settle();
+    }
+  };
+  unsigned age = 0;
   for (;;) {
     if (!__any(active)) break;
     int e_key = -1;
@@ -808,7 +823,7 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
       if (stored) {
         // the forward's exit of this step (a next cell outside the scene,
         // which only a trace from another walk could hold, ends the ray)
-        const int2 e = xt.p[(size_t)k * xt.stride];
+        const int2 e = kCarry ? e0 : xt.p[(size_t)k * xt.stride];
         ex.t = __int_as_float(e.x);
         ex.next = e.y >= 0 && e.y < s.n ? e.y : -1;
         ex.redecided = false;
@@ -825,18 +840,27 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
         if (!stored) ex = step_exit<LPR>(s, w, r, c, cur, t_in, sub);
       }
       float4 pn = here;
-      if constexpr (kCarry) pn = ex.next >= 0 ? s.cells[2 * (size_t)ex.next] : here;
+      float cr, cg, cb;
+      if constexpr (kCarry) {
+        quad_rgb<TEX>(tx, tp, cr, cg, cb);
+        if (stored) {
+          pn = ahead;
+          e0 = e1;
+          if (k + 2 < xt.cap) e1 = xt.p[(size_t)(k + 2) * xt.stride];
+          if (k + 1 < xt.cap && e0.y >= 0 && e0.y < s.n) ahead = s.cells[2 * (size_t)e0.y];
+        } else if (ex.next >= 0) {
+          pn = s.cells[2 * (size_t)ex.next];
+        }
+        if (ex.next >= 0) tx.load(s.texels, (size_t)ex.next * (size_t)RR + (size_t)tp.base, R);
+      }
       cnt.redecide += ex.redecided ? 1u : 0u;
       cnt.deg += (uint32_t)c.deg;
       const Segment sg = segment(ex.t, r.tmax, t_in, c.sigma);
       const float wk = T * sg.alpha;
-      float cr, cg, cb;
       Taps ts = tp;
       float gxx = 0.0f, gxy = 0.0f, gxz = 0.0f, dldt = 0.0f;
       float glr = 0.0f, glg = 0.0f, glb = 0.0f;
-      if constexpr (APP == 0) {
-        texel_rgb<TEX>(s.texels, cur, R, tp, cr, cg, cb);
-      } else {
+      if constexpr (APP == 1) {
         float hx, hy, hz;
         hit_vector(r, c, k, t_in, ex.t, hx, hy, hz);
         const bool on_site = hx == 0.0f && hy == 0.0f && hz == 0.0f;
@@ -1020,18 +1044,18 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
         if constexpr (kCarry) here = pn;
       }
     }
-    emit_records<LPR, 0, APP == 1, CAP>(e_key, e_ds, e_px, e_py, e_pz, e_tp, e_mr, e_mg, e_mb, lane,
-                                   RR, R, g, tab, ob);
+    emit_records<0>(e_key, e_ds, e_px, e_py, e_pz, e_tp, e_mr, e_mg, e_mb, lane,
+                                   RR, R, g, tab, area, age++, settle);
     if constexpr (APP == 1)
-      emit_records<LPR, 4, true, CAP>(v_key, 0.0f, 0.0f, 0.0f, 0.0f, tp, v_mr, v_mg, v_mb, lane, RR, R,
-                                 g, tab, ob);
+      emit_records<4>(v_key, 0.0f, 0.0f, 0.0f, 0.0f, tp, v_mr, v_mg, v_mb, lane, RR, R,
+                                 g, tab, area, age, [] {});
   }
   // the last visited cell, and the unvisited cell behind an early-stopped ray's exit face
-  emit_records<LPR, 0, APP == 1, CAP>(lead && a_cell >= 0 ? (a_cell * MAPS) * RR + a_tp.base : -1,
+  emit_records<0>(lead && a_cell >= 0 ? (a_cell * MAPS) * RR + a_tp.base : -1,
                                  a_ds, a_px, a_py, a_pz, a_tp, a_mr, a_mg, a_mb, lane, RR, R, g,
-                                 tab, ob);
-  emit_records<LPR, 0, APP == 1, CAP>(lead && c_cell >= 0 ? (c_cell * MAPS) * RR + tp.base : -1, 0.0f,
-                                 c_px, c_py, c_pz, tp, 0.0f, 0.0f, 0.0f, lane, RR, R, g, tab, ob);
+                                 tab, area, age, [] {});
+  emit_records<0>(lead && c_cell >= 0 ? (c_cell * MAPS) * RR + tp.base : -1, 0.0f,
+                                 c_px, c_py, c_pz, tp, 0.0f, 0.0f, 0.0f, lane, RR, R, g, tab, area, age, [] {});
 }
 
 }  // namespace voro
