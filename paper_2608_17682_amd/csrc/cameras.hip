@@ -194,14 +194,16 @@ __device__ __forceinline__ void write_ray_out(const ViewsArgs& a, const TileRay&
 // wave of the grid takes one tile (workgroups renumbered per XCD) and the
 // hardware dispatcher balances the load.  One lane per ray walks with staged
 // edge rows (dynamic LDS: kStageBytesPerWave per wave), also when gathered
-// rows are ranked in half precision.  The persistent one-lane-per-ray exact walk is
-// held to 96 VGPRs, five waves per SIMD instead of four (the registers come
-// from the FP64 branch, the per-view focal length and the per-tile counters;
-// its few spills, 48 bytes per lane, sit outside the walk loop); the extra
-// wave hides more of the gathers' latency.
+// rows are ranked in half precision; the grid's rows leave out the faces that
+// point away from the tile's rays (the persistent queue's do not: its camera
+// state fills the registers, and the 4M-site forward lost 1%).  The exact
+// one-lane-per-ray walks are held to 96 VGPRs, five waves per SIMD, at the
+// price of a few spills around the walk loop (100k-site frame 592 us at four,
+// 556 at five, 574 at six); spherical harmonics need 128 (at 96: 1029 us).
 template <int LPR, int APP, bool PERSIST, bool E16>
 struct FwdWaves {
-  static constexpr int value = (LPR == 1 && APP == 0 && (PERSIST ? !E16 : E16)) ? 5 : 1;
+  static constexpr int value =
+      LPR > 1 ? 1 : APP == 0 ? (PERSIST && E16 ? 1 : 5) : APP == 1 ? (E16 ? 1 : 5) : 4;
 };
 
 template <int LPR, int TEX, int APP, bool PERSIST, bool E16>
@@ -235,7 +237,7 @@ __global__ void __launch_bounds__(256)
     if constexpr (LPR == 1) {
       RayIn r{};
       if (has) r = views_ray(a, tr, &capped);
-      const RayOut out = walk_forward_staged<TEX, APP, E16>(
+      const RayOut out = walk_forward_staged<TEX, APP, E16, !PERSIST>(
           a.s, a.w, r, has, lane, slabs + wave * (kStageBytesPerWave / 16), nullptr, 0, cnt,
           false, ray_trace(a, has, tr.ray));
       if (has) write_ray_out<LPR>(a, tr, out);
@@ -309,7 +311,7 @@ __global__ void __launch_bounds__(256) k_views_fwd_refill(ViewsArgs a) {
         if (q >= pool) break;
         continue;
       }
-      if (active && fwd_step<1, TEX, APP, E16>(st, a.s, a.w, r, 0, nullptr, 0, cnt, false, nullptr,
+      if (active && fwd_step<1, TEX, APP, E16>(st, a.s, a.w, r, 0, nullptr, 0, cnt, false, nullptr, 0,
                                                ray_trace(a, true, tr.ray))) {
         write_ray_out<1>(a, tr, fwd_end<APP>(st, true, cnt));
         active = false;
@@ -475,7 +477,7 @@ static CamTable make_table(const voro_camera* cams, int V, int tile_w, int tile_
 // dynamic LDS of a forward launch: the staged edge rows of each wave
 template <int LPR>
 static size_t fwd_lds(int block) {
-  return LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave : 0;
+  return LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave + kStagePad : 0;
 }
 
 template <int LPR, int TEX, int APP, bool E16 = false>

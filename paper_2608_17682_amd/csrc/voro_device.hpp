@@ -102,7 +102,9 @@ __device__ __forceinline__ void best_merge(Best& r, float u1, int k1, float u2) 
   r.j1 = take ? k1 : r.j1;
 }
 
-template <int LPR>
+// PADDED (one lane per ray): three records past the row can be read, and are
+// left out: the tail then takes one trip to memory instead of up to three.
+template <int LPR, bool PADDED = false>
 __device__ __forceinline__ Best exit_search(const float4* __restrict__ edges, int off, int deg,
                                             int sub, float qx, float qy, float qz, float dx,
                                             float dy, float dz) {
@@ -122,7 +124,14 @@ __device__ __forceinline__ Best exit_search(const float4* __restrict__ edges, in
       best_push(r, cross_u(E3, q2x, q2y, q2z, dx, dy, dz), __float_as_int(E3.w));
     }
     const int rem = deg - full;
-    if (rem > 0) {
+    if (PADDED && rem > 0) {
+      const float4 E0 = e[full], E1 = e[full + 1], E2 = e[full + 2];
+      const float u1 = cross_u(E1, q2x, q2y, q2z, dx, dy, dz);
+      const float u2 = cross_u(E2, q2x, q2y, q2z, dx, dy, dz);
+      best_push(r, cross_u(E0, q2x, q2y, q2z, dx, dy, dz), __float_as_int(E0.w));
+      best_push(r, rem > 1 ? u1 : kInf, __float_as_int(E1.w));
+      best_push(r, rem > 2 ? u2 : kInf, __float_as_int(E2.w));
+    } else if (rem > 0) {
       const float4 E0 = e[full];
       best_push(r, cross_u(E0, q2x, q2y, q2z, dx, dy, dz), __float_as_int(E0.w));
       if (rem > 1) {

@@ -147,7 +147,7 @@ __device__ __forceinline__ void wg_stats_flush(const unsigned long long* s,
 template <int LPR, bool E16 = false>
 __device__ __forceinline__ Exit step_exit(const DevScene& s, const WalkParams& w, const RayIn& r,
                                           const Cell& c, int cur, float t_in, int sub,
-                                          const float4* lrow = nullptr) {
+                                          const float4* lrow = nullptr, int llen = 0) {
   const float qx = fmaf(t_in, r.dx, r.ox) - c.px;
   const float qy = fmaf(t_in, r.dy, r.oy) - c.py;
   const float qz = fmaf(t_in, r.dz, r.oz) - c.pz;
@@ -181,7 +181,7 @@ __device__ __forceinline__ Exit step_exit(const DevScene& s, const WalkParams& w
   }
   if (searched) {
   } else if (LPR == 1 && lrow) {
-    b = exit_search<1>(lrow, 0, c.deg, 0, qx, qy, qz, r.dx, r.dy, r.dz);
+    b = exit_search<1, true>(lrow, 0, llen, 0, qx, qy, qz, r.dx, r.dy, r.dz);
   } else {
     b = exit_search<LPR>(s.edges, c.off, c.deg, sub, qx, qy, qz, r.dx, r.dy, r.dz);
   }
@@ -261,11 +261,11 @@ __device__ __forceinline__ bool fwd_step(FwdState<APP>& st, const DevScene& s,
                                          const WalkParams& w, const RayIn& r, int sub,
                                          int32_t* rec, int max_record, Counters& cnt,
                                          bool dist_on, const float4* lrow = nullptr,
-                                         const ExitTrace& xt = {}) {
+                                         int llen = 0, const ExitTrace& xt = {}) {
   const int cur = st.cur;
   const float t_in = st.t_in;
   const Cell c = st.nc;
-  const Exit ex = step_exit<LPR, E16>(s, w, r, c, cur, t_in, sub, lrow);
+  const Exit ex = step_exit<LPR, E16>(s, w, r, c, cur, t_in, sub, lrow, llen);
   if (xt.p && sub == 0 && st.k < xt.cap) {
     // streamed out (only the adjoint reads it back): a non-temporal store
     // leaves the caches to the walk's records
@@ -352,69 +352,168 @@ __device__ __forceinline__ RayOut walk_forward(const DevScene& s, const WalkPara
   const bool walk = fwd_begin<APP>(st, s, r, cnt);
   if (walk)
     while (!fwd_step<LPR, TEX, APP, E16>(st, s, w, r, sub, rec, max_record, cnt, dist_on,
-                                         nullptr, xt)) {
+                                         nullptr, 0, xt)) {
     }
   return fwd_end<APP>(st, walk, cnt);
 }
 
 // Wave-cooperative staging of edge rows (one lane per ray).  Rays of a
-// coherent tile often stand in the same few cells: when the live lanes of
-// the wave sit in at most kStageCells distinct cells whose rows (at most 64
-// faces each) fit the wave's LDS slab together, the wave copies those rows
-// into the slab, one coalesced load per row, and every live lane reads its
-// row from there; otherwise each lane gathers its own row from global
-// memory.  The choice is per wave and step (mixing both within one step was
-// slower: the two loops then run one after the other), and the exit search
-// sees the same records in the same order either way.
+// coherent tile often stand in the same few cells (6 distinct ones a step on
+// the 100k-site scene, 78% of the steps within 8): when the live lanes of the
+// wave sit in at most kStageCells distinct cells whose rows fit the wave's LDS
+// slab together, the wave copies those rows into the slab, packed, 64 records
+// a load with all loads under way at once, and every live lane reads its row
+// from there; otherwise each lane gathers its own row from global memory.  The
+// choice is per wave and step (mixing both within one step was slower: the two
+// loops then run one after the other), and the exit search sees the same
+// records in the same order either way, less those that cannot be an exit:
+// on the grid schedule, whose waves hold one small screen tile, the faces that
+// point away from every ray of the wave (about half) never reach the slab.
+//
+// The 100k-site frame is bound by VALU issue (0.74 of it before), 14
+// instructions per face: 577 -> 541 us, two maps 1280x840 922 -> 836 us,
+// spherical harmonics 775 -> 713 us.  Sixteen cells instead of eight: 807 us
+// (registers); loading each texel ahead of the search: 580 us; groups of eight
+// records in flight in the gathered search: 638 us (one wave per SIMD less).
 constexpr int kStageCells = 8;
 constexpr int kStageRecords = 256;
 constexpr int kStageBytesPerWave = kStageRecords * 16;
+constexpr int kStagePad = 64;  // behind the last slab: a search reads three records past its row
 constexpr int kStageMaxGap = 8;
 
+// The directions of a wave's rays: centre c and a radius with |w - c| <= rho
+// for every ray (wave-uniform).
+struct Cone {
+  float cx, cy, cz, rho;
+};
+
+__device__ __forceinline__ float wave_uniform(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
+__device__ __forceinline__ Cone wave_cone(const RayIn& r, bool has) {
+  float x = has ? r.dx : 0.0f, y = has ? r.dy : 0.0f, z = has ? r.dz : 0.0f;
+  float n = has ? 1.0f : 0.0f;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    x += __shfl_xor(x, m);
+    y += __shfl_xor(y, m);
+    z += __shfl_xor(z, m);
+    n += __shfl_xor(n, m);
+  }
+  const float inv = 1.0f / fmaxf(n, 1.0f);
+  Cone k;
+  k.cx = wave_uniform(x * inv);
+  k.cy = wave_uniform(y * inv);
+  k.cz = wave_uniform(z * inv);
+  float d = has ? fabsf(r.dx - k.cx) + fabsf(r.dy - k.cy) + fabsf(r.dz - k.cz) : 0.0f;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) d = fmaxf(d, __shfl_xor(d, m));
+  // max |w - c|_inf <= |w - c|_1; the last term covers the FP32 roundings
+  k.rho = wave_uniform(d * 1.0001f + 4e-6f);
+  return k;
+}
+
 // Every lane of the wave must call this; alive: the lane's walk goes on, at
-// cell cur with record c.  Returns the lane's staged row, or null when the
-// wave's rows were not staged (then staged = false on every lane).
+// cell cur with record c.  Returns the lane's staged row and its length, or
+// null when the wave's rows were not staged (then staged = false on every
+// lane).  CULL: faces that no ray of the wave can leave through (m.w < 0 over
+// the whole cone) are left out of the slab.
+template <bool CULL>
 __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ edges, float4* slab,
-                                                    bool alive, int cur, const Cell& c, int lane,
+                                                    bool alive, int cur, const Cell& c,
+                                                    const Cone& cone, int lane, int& len,
                                                     bool& staged) {
   unsigned long long pend = __ballot(alive);
   int mine = 0;
-  int offs[kStageCells], degs[kStageCells];
+  int from[kStageCells], delta[kStageCells];  // first record of each row; its source less that
   int n = 0, used = 0;
-  bool fits = true;
 #pragma unroll
   for (int q = 0; q < kStageCells; ++q) {
     if (pend == 0ull) break;
     const int leader = __ffsll((long long)pend) - 1;  // wave-uniform
     const int cl = __builtin_amdgcn_readlane(cur, leader);
-    offs[q] = __builtin_amdgcn_readlane(c.off, leader);
-    degs[q] = __builtin_amdgcn_readlane(c.deg, leader);
+    const int deg = __builtin_amdgcn_readlane(c.deg, leader);
+    from[q] = used;
+    delta[q] = __builtin_amdgcn_readlane(c.off, leader) - used;
     const bool same = alive && cur == cl;
     pend &= ~__ballot(same);
-    if (same) mine = used;
-    fits = fits && degs[q] <= 64;
-    used += degs[q];
+    mine = same ? (CULL ? q : used) : mine;  // the row's number, or its start
+    used += deg;
     n = q + 1;
   }
-  staged = pend == 0ull && fits && used <= kStageRecords;
+  staged = pend == 0ull && used <= kStageRecords;
   if (!staged) return nullptr;
   // the slab's previous rows have been read by every lane (LDS operations of
   // one wave complete in order)
   __builtin_amdgcn_wave_barrier();
-  int base = 0;
+  // the rows end to end, 64 records a load, every load under way before the
+  // first is used
+  constexpr int kLoads = kStageRecords / 64;
+  float4 v[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    if (64 * i >= used) break;
+    const int r = 64 * i + lane;
+    int d = delta[0];
+#pragma unroll
+    for (int q = 1; q < kStageCells; ++q) {
+      if (q >= n) break;
+      d = r >= from[q] ? delta[q] : d;
+    }
+    v[i] = edges[r < used ? r + d : 0];
+  }
+  if constexpr (!CULL) {
+    len = c.deg;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      if (64 * i >= used) break;
+      slab[64 * i + lane] = v[i];
+    }
+    __builtin_amdgcn_wave_barrier();
+    return slab + mine;
+  }
+  int start[kStageCells];
+#pragma unroll
+  for (int q = 0; q < kStageCells; ++q) start[q] = 0;
+  int kept = 0;
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    if (64 * i >= used) break;
+    const float4 E = v[i];
+    const float b = dot3(E.x, E.y, E.z, cone.cx, cone.cy, cone.cz);
+    const float e = fabsf(E.x) + fabsf(E.y) + fabsf(E.z);
+    const bool keep = 64 * i + lane < used && !(fmaf(e, cone.rho, b) < 0.0f);
+    const unsigned long long m = __ballot(keep);
+    const int at = kept + __popcll(m & ((1ull << lane) - 1ull));
+    if (keep) slab[at] = E;
+#pragma unroll
+    for (int q = 1; q < kStageCells; ++q) {
+      if (q >= n) break;
+      const int lo = from[q] - 64 * i;
+      if (lo > 0) start[q] = kept + (int)__popcll(lo >= 64 ? m : m & ((1ull << lo) - 1ull));
+    }
+    kept += (int)__popcll(m);
+  }
+  // each lane's row: start and length by the row's number
+  int rows = 0;
 #pragma unroll
   for (int q = 0; q < kStageCells; ++q) {
-    if (q < n && lane < degs[q]) slab[base + lane] = edges[offs[q] + lane];
-    base += q < n ? degs[q] : 0;
+    if (q >= n) break;
+    const int end = q + 1 < n ? start[q + 1 < kStageCells ? q + 1 : 0] : kept;
+    const int w = start[q] | ((end - start[q]) << 16);
+    rows = lane == q ? w : rows;
   }
+  rows = __builtin_amdgcn_ds_bpermute(4 * mine, rows);
+  len = rows >> 16;
   __builtin_amdgcn_wave_barrier();
-  return slab + mine;
+  return slab + (rows & 0xffff);
 }
 
 // walk_forward with one lane per ray and staged rows.  Every lane of the
 // wave must call this (has_ray = false for lanes without a ray); slab: the
 // wave's kStageBytesPerWave of LDS.
-template <int TEX, int APP, bool E16 = false>
+template <int TEX, int APP, bool E16 = false, bool CULL = false>
 __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const WalkParams& w,
                                                       const RayIn& r, bool has_ray, int lane,
                                                       float4* slab, int32_t* rec, int max_record,
@@ -423,6 +522,8 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
   FwdState<APP> st;
   const bool walk = has_ray && fwd_begin<APP>(st, s, r, cnt);
   bool alive = walk;
+  Cone cone{};
+  if constexpr (CULL) cone = wave_cone(r, walk);
   // after a step whose rows could not be staged the wave waits `wait` steps
   // before it tries again, doubling the wait up to kStageMaxGap while it
   // keeps failing (rays that have spread apart seldom meet again soon, and
@@ -430,12 +531,13 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
   int wait = 0, gap = 1;
   while (__any(alive)) {
     const float4* row = nullptr;
+    int len = 0;
     if (wait == 0) {
       // the row bounds for the staging (the record fwd_step will use)
       Cell c;
       if (alive) c = st.nc;
       bool staged;
-      row = stage_rows(s.edges, slab, alive, st.cur, c, lane, staged);
+      row = stage_rows<CULL>(s.edges, slab, alive, st.cur, c, cone, lane, len, staged);
       if (staged) {
         gap = 1;
       } else {
@@ -447,10 +549,10 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
     }
     if (alive) {
       if (row)
-        alive = !fwd_step<1, TEX, APP, E16>(st, s, w, r, 0, rec, max_record, cnt, dist_on, row, xt);
+        alive = !fwd_step<1, TEX, APP, E16>(st, s, w, r, 0, rec, max_record, cnt, dist_on, row, len, xt);
       else
         alive =
-            !fwd_step<1, TEX, APP, E16>(st, s, w, r, 0, rec, max_record, cnt, dist_on, nullptr, xt);
+            !fwd_step<1, TEX, APP, E16>(st, s, w, r, 0, rec, max_record, cnt, dist_on, nullptr, 0, xt);
     }
   }
   return fwd_end<APP>(st, walk, cnt);
@@ -758,7 +860,10 @@ __device__ __forceinline__ void walk_backward(const DevScene& s, const WalkParam
   }
   if (active) cnt.rays++;
   const bool lead = sub == 0;
-  const Taps tp = ray_taps<APP>(r, R);
+  // no weights without a ray: its direction is none, and a NaN in an idle lane
+  // would send the whole wave's records past the merge
+  Taps tp{};
+  if (active) tp = ray_taps<APP>(r, R);
   float T = 1.0f, Pr = 0.0f, Pg = 0.0f, Pb = 0.0f, t_in = 0.0f;
   float dW = 0.0f, dA = 0.0f, dGW = 0.0f, s0 = 0.0f;  // distortion prefix sums
   int cur = active ? r.start : 0;
