@@ -143,7 +143,9 @@ typedef struct voro_scene {
  *               comparison model of Sec. 3.3 (needs tex_maps = 3; forward
  *               only)
  *   lanes_per_ray  1, 2, 4, 8 or 16 lanes cooperate on one ray's
- *               neighbour tests (0 = library default)                   [0]
+ *               neighbour tests (0 = library default: one lane, or as many
+ *               as fill the GPU when a call has few rays; results do not
+ *               depend on it)                                           [0]
  *   tile_w, tile_h  screen tile walked by one 64-lane wave, in rays;
  *               tile_w * tile_h * lanes_per_ray must equal 64 (0 = default)
  *   img_w       voro_render_fwd/bwd: when > 0 the R rays are row-major

@@ -100,11 +100,18 @@ def lookup(ds, cams, direction: str) -> Optional[dict]:
     return lookup_key(key_of(ds, cams, direction))
 
 
+# rays up to which a launch leaves its shape to the library, which then splits
+# each ray over several lanes to fill the GPU (the table is tuned on launches
+# of a million rays and more)
+SMALL_LAUNCH = {"fwd": 1 << 17, "bwd": 1 << 16}
+
+
 def params_for(ds, cams, direction: str):
     """voro_params with the library defaults and the tuned launch shape (if any)."""
     from . import voro
     p = voro.default_params()
-    t = lookup(ds, cams, direction)
+    rays = sum(int(c.width) * int(c.height) * int(c.spp) for c in cams)
+    t = lookup(ds, cams, direction) if rays > SMALL_LAUNCH[direction] else None
     if t:
         for k, v in t.items():
             setattr(p, k, v)

@@ -131,9 +131,27 @@ voro_status check_appearance(const voro_scene* s, const voro_params* p) {
   return VORO_OK;
 }
 
-Launch resolve_launch(const voro_params* p) {
+// Lanes per ray where the caller leaves them open.  One lane per ray needs
+// kFillFwd rays to keep the chip's 1024 SIMDs at four waves; with fewer, each
+// ray's neighbour tests are split over as many lanes as fill it (measured on
+// one MI355X, 100k sites, forward: 4,096 rays 230 us with one lane, 97 with
+// 16; 32,400 rays 244 with one, 120 with eight; 131,071 rays 450 with one, 381
+// with two; 262,144 rays 332 with one, 360 with two).  The adjoint, which
+// splits only its searches, gains up to kFillBwd (4,096 rays 403 with one, 184
+// with 16; 65,536 rays 268 with one, 253 with two; 129,600 rays 301 with one,
+// 380 with two).  A tile size or a variant with one lane only keeps one.
+static int default_lanes(const voro_params* p, int64_t rays, bool backward) {
+  constexpr int64_t kFillFwd = 1 << 18, kFillBwd = 1 << 17;
+  if (p->tile_w > 0 || p->edge_fp16 || p->schedule == VORO_SCHEDULE_REFILL) return 1;
+  const int64_t fill = backward ? kFillBwd : kFillFwd;
+  int lanes = 1;
+  while (lanes < 16 && 2 * lanes * rays <= fill) lanes *= 2;
+  return lanes;
+}
+
+Launch resolve_launch(const voro_params* p, int64_t rays, bool backward) {
   Launch L;
-  L.lpr = p->lanes_per_ray == 0 ? 1 : p->lanes_per_ray;
+  L.lpr = p->lanes_per_ray == 0 ? default_lanes(p, rays, backward) : p->lanes_per_ray;
   L.block = p->block == 0 ? 256 : p->block;
   if (p->tile_w > 0) {
     L.tile_w = p->tile_w;

@@ -15,8 +15,6 @@
 
 namespace voro {
 
-voro_status launch_locate_brute(const voro_scene* scene, void* partials, const float* origins,
-                                int U, int32_t* out, hipStream_t st);
 float4* cell_grads(const voro_scene* s, void* ws);
 
 // ------------------------------------------------------------- gen_rays
@@ -51,8 +49,8 @@ __global__ void __launch_bounds__(256) k_gen_rays(CamTable ct, float* __restrict
 // neighbouring samples.  Workgroup b runs on XCD b % 8; each XCD first
 // drains its own contiguous eighth of the tile sequence (its L2 sees one
 // image region), then helps the other XCDs.  Counters live in the workspace
-// and are zeroed by k_views_setup before every launch.
-constexpr int kXcd = 8;
+// and are zeroed by k_views_locate before every launch.
+constexpr int kXcd = kViewsQueues;
 
 struct ViewsArgs {
   DevScene s;
@@ -91,18 +89,6 @@ __device__ __forceinline__ ExitTrace ray_trace(const ViewsArgs& a, bool has, int
   x.stride = a.n_rays;
   x.cap = a.trace_cap;
   return x;
-}
-
-struct Centers {
-  float c[3 * VORO_MAX_VIEWS];
-};
-
-// camera centres into the workspace (they travel as kernel arguments, so no
-// host-to-device copy is needed) and the tile counters zeroed
-__global__ void k_views_setup(Centers c, float* dst, int n, unsigned int* ctr) {
-  const int i = threadIdx.x;
-  if (i < n) dst[i] = c.c[i];
-  if (i < kXcd) ctr[i] = 0u;
 }
 
 // Next work unit from the XCD-partitioned queue (one thread asks), or -1
@@ -574,17 +560,16 @@ static void launch_views_tex(int tex, int lpr, bool backward, bool persist, cons
   }
 }
 
-// Scratch of a multi-view launch: the tile-queue counters, the camera
-// centres and their cells, and the brute-force search's partial results.
+// Scratch of a multi-view launch: the tile-queue counters and the ticket, the
+// cells of the camera centres, and the brute-force search's partial results.
 constexpr size_t kViewsScratchCounters = 0;
 constexpr size_t kViewsScratchCenters = 256;
-constexpr size_t kViewsScratchOrigins = 512;
-constexpr size_t kViewsScratchPartials = 768;
+constexpr size_t kViewsScratchPartials = 512;
 constexpr size_t kViewsScratchBytes =
     kViewsScratchPartials + (size_t)VORO_MAX_VIEWS * kLocateChunks * 16;
-static_assert(kViewsScratchCenters >= kXcd * 4 && kViewsScratchOrigins - kViewsScratchCenters >=
-              VORO_MAX_VIEWS * 4 && kViewsScratchPartials - kViewsScratchOrigins >=
-              3 * VORO_MAX_VIEWS * 4, "views scratch layout");
+static_assert(kViewsTicket >= kXcd * 4 && kViewsScratchCenters >= kViewsTicket + 4 &&
+              kViewsScratchPartials - kViewsScratchCenters >= VORO_MAX_VIEWS * 4,
+              "views scratch layout");
 
 // Where a launch keeps its scratch: counters, centres and their cells at
 // `base` (kViewsScratchPartials bytes), the partial results at `partials`.
@@ -622,13 +607,12 @@ static voro_status views_common(bool backward, const voro_scene* scene, const vo
   for (int v = 0; v < V; ++v) spp = spp || cams[v].spp > 1;
   *any_spp = spp;
   if ((st = check_device()) != VORO_OK) return st;
-  const Launch L = resolve_launch(params);
+  const Launch L = resolve_launch(params, *n_rays, backward);
   a.trace = reinterpret_cast<int2*>(trace);
   a.trace_cap = trace ? trace_cap : 0;
   a.n_rays = (unsigned)*n_rays;
   a.counters = reinterpret_cast<unsigned int*>(sc.base + kViewsScratchCounters);
   int32_t* centers = reinterpret_cast<int32_t*>(sc.base + kViewsScratchCenters);
-  float* origins = reinterpret_cast<float*>(sc.base + kViewsScratchOrigins);
   a.center_cell = centers;
   a.s = dev_scene(scene, ws);
   a.w = walk_params(params);
@@ -642,16 +626,16 @@ static voro_status views_common(bool backward, const voro_scene* scene, const vo
   a.tile_w = L.tile_w;
   a.tile_h = L.tile_h;
   const hipStream_t s = (hipStream_t)stream;
-  // camera centres -> device (through kernel arguments), then their cells
-  Centers cc;
+  ViewCenters cc;
   for (int v = 0; v < V; ++v) {
     cc.c[3 * v] = cams[v].c2w[3];
     cc.c[3 * v + 1] = cams[v].c2w[7];
     cc.c[3 * v + 2] = cams[v].c2w[11];
   }
-  hipLaunchKernelGGL(k_views_setup, dim3(1), dim3(64), 0, s, cc, origins, 3 * V, a.counters);
-  if ((st = check_launch("views: setup")) != VORO_OK) return st;
-  if ((st = launch_locate_brute(scene, sc.partials, origins, V, centers, s)) != VORO_OK) return st;
+  if ((st = launch_views_locate(scene, sc.partials, cc, V,
+                                reinterpret_cast<unsigned*>(sc.base + kViewsTicket), a.counters,
+                                centers, s)) != VORO_OK)
+    return st;
   const int block = L.block;
   // the refill schedule drives the one-lane-per-ray forward; the adjoint
   // (whose work unit is a workgroup tile) takes the persistent queue then

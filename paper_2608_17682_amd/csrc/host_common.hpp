@@ -27,6 +27,13 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // and density gradients (one float4 per cell, zero between adjoint calls).
 constexpr int kLocateBruteMax = 64;    // origins searched by brute force
 constexpr int kLocateChunks = 256;     // max partial results per origin
+constexpr int kViewsQueues = 8;        // tile-queue counters of a multi-view launch (one per XCD)
+constexpr size_t kViewsTicket = 64;    // offset of its ticket in the counter region
+
+// camera centres of a multi-view launch, passed as a kernel argument
+struct ViewCenters {
+  float c[3 * VORO_MAX_VIEWS];
+};
 struct WsLayout {
   size_t cells, edges, edges16, locate, counters, cellg, total;
 };
@@ -42,6 +49,11 @@ inline WsLayout ws_layout(int32_t n, int64_t m) {
   L.total = align256(L.cellg + (size_t)n * 16);
   return L;
 }
+
+// cells of the camera centres of a multi-view launch (defined in locate.hip)
+voro_status launch_views_locate(const voro_scene* scene, void* partials, const ViewCenters& c,
+                                int V, unsigned* ticket, unsigned* queue, int32_t* out,
+                                hipStream_t st);
 
 // adds the workspace's per-cell accumulator into g_sites / g_density and
 // clears it (stream-ordered after an adjoint kernel; defined in walk.hip)
@@ -66,10 +78,10 @@ inline voro_status check_trace(const int32_t* trace, int32_t trace_cap) {
   return VORO_OK;
 }
 
-// effective launch parameters after defaults
+// effective launch parameters of a launch over `rays` rays after defaults
 struct Launch {
   int lpr, tile_w, tile_h, block;
 };
-Launch resolve_launch(const voro_params* p);
+Launch resolve_launch(const voro_params* p, int64_t rays, bool backward);
 
 }  // namespace voro

@@ -30,6 +30,7 @@ struct PrepArgs {
   float4* edges;
   uint2* edges16;
   float4* cellg;  // the adjoint's per-cell accumulator, cleared here
+  unsigned* ticket;  // the multi-view launch's ticket, cleared here
   unsigned long long* stats;
 };
 
@@ -37,6 +38,7 @@ __global__ void __launch_bounds__(256) k_prepare(PrepArgs a) {
   const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const long cell = gid >> 4;
   const int l16 = threadIdx.x & 15;
+  if (gid == 0) *a.ticket = 0u;
   if (cell >= a.n) return;
   const int i = (int)cell;
   const int off = a.nbr_off[i];
@@ -366,7 +368,7 @@ static voro_status ray_launch(bool backward, const voro_scene* scene, const void
   if (params->img_w > 0 && (R % params->img_w) != 0)
     return fail(VORO_EINVAL, "R (%d) must be a multiple of img_w (%d)", R, params->img_w);
   if ((st = check_device()) != VORO_OK) return st;
-  const Launch L = resolve_launch(params);
+  const Launch L = resolve_launch(params, R, backward);
   a.s = dev_scene(scene, ws);
   a.w = walk_params(params);
   set_grad_layout(a.g, scene);
@@ -422,6 +424,7 @@ voro_status voro_prepare(const voro_scene* scene, void* ws, size_t ws_bytes, uin
   a.edges = reinterpret_cast<float4*>((char*)ws + L.edges);
   a.edges16 = reinterpret_cast<uint2*>((char*)ws + L.edges16);
   a.cellg = reinterpret_cast<float4*>((char*)ws + L.cellg);
+  a.ticket = reinterpret_cast<unsigned*>((char*)ws + L.counters + kViewsTicket);
   a.stats = reinterpret_cast<unsigned long long*>(stats);
   const long threads = (long)scene->n_sites * 16;
   const int blocks = (int)((threads + 255) / 256);
