@@ -180,12 +180,11 @@ __device__ __forceinline__ void write_ray_out(const ViewsArgs& a, const TileRay&
 // wave of the grid takes one tile (workgroups renumbered per XCD) and the
 // hardware dispatcher balances the load.  One lane per ray walks with staged
 // edge rows (dynamic LDS: kStageBytesPerWave per wave), also when gathered
-// rows are ranked in half precision; the grid's rows leave out the faces that
-// point away from the tile's rays (the persistent queue's do not: its camera
-// state fills the registers, and the 4M-site forward lost 1%).  The exact
-// one-lane-per-ray walks are held to 96 VGPRs, five waves per SIMD, at the
-// price of a few spills around the walk loop (100k-site frame 592 us at four,
-// 556 at five, 574 at six); spherical harmonics need 128 (at 96: 1029 us).
+// rows are ranked in half precision.  The exact one-lane-per-ray walks are
+// held to 96 VGPRs, five waves per SIMD, at the price of spills around the
+// walk loop (100k-site frame 592 us at four waves, 556 at five, 574 at six;
+// 4M-site persistent forward + backward 54.3 ms at five, 56.0 at four);
+// spherical harmonics need 128 (at 96: 1029 us instead of 708).
 template <int LPR, int APP, bool PERSIST, bool E16>
 struct FwdWaves {
   static constexpr int value =
@@ -223,7 +222,7 @@ __global__ void __launch_bounds__(256)
     if constexpr (LPR == 1) {
       RayIn r{};
       if (has) r = views_ray(a, tr, &capped);
-      const RayOut out = walk_forward_staged<TEX, APP, E16, !PERSIST>(
+      const RayOut out = walk_forward_staged<TEX, APP, E16>(
           a.s, a.w, r, has, lane, slabs + wave * (kStageBytesPerWave / 16), nullptr, 0, cnt,
           false, ray_trace(a, has, tr.ray));
       if (has) write_ray_out<LPR>(a, tr, out);
@@ -463,7 +462,7 @@ static CamTable make_table(const voro_camera* cams, int V, int tile_w, int tile_
 // dynamic LDS of a forward launch: the staged edge rows of each wave
 template <int LPR>
 static size_t fwd_lds(int block) {
-  return LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave + kStagePad : 0;
+  return LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave : 0;
 }
 
 template <int LPR, int TEX, int APP, bool E16 = false>

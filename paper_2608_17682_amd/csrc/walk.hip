@@ -313,7 +313,7 @@ template <int LPR, int TEX, int APP>
 static void launch_ray_kernel(bool backward, const RayArgs& a, int blocks, int block,
                               hipStream_t st) {
   if (!backward) {
-    const size_t lds = LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave + kStagePad : 0;
+    const size_t lds = LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave : 0;
     if constexpr (LPR == 1) {
       if (a.w.edge16) {
         hipLaunchKernelGGL((k_render_fwd<1, TEX, APP, true>), dim3(blocks), dim3(block), lds, st,

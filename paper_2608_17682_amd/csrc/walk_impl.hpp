@@ -357,33 +357,81 @@ __device__ __forceinline__ RayOut walk_forward(const DevScene& s, const WalkPara
   return fwd_end<APP>(st, walk, cnt);
 }
 
+// Orders a wave's own LDS accesses for the compiler (the hardware keeps them in
+// order).
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Ranks the distinct keys of the lanes with `open`: each such lane writes its
+// number to a bucket chosen by its key and reads back whose stayed; lanes whose
+// key is that lane's have their leader, the others go on with another hash.
+// Every round settles at least one key.  Every lane of the wave must call this;
+// bucket: 256 bytes of the wave's LDS.  rank: of the lane's key (-1: not open),
+// leads: the lane that stands for its key.  Stops, and returns a number above
+// `most`, once there are more than `most` keys.
+__device__ __forceinline__ int rank_keys(int key, bool open, unsigned char* bucket, int lane,
+                                         int most, int& rank, bool& leads) {
+  rank = -1;
+  leads = false;
+  int total = 0;
+  unsigned mul = 2654435761u;
+  do {
+    const unsigned h = ((unsigned)key * mul) >> 24;
+    int lead = lane;
+    if (open) bucket[h] = (unsigned char)lane;
+    lds_order();
+    if (open) lead = bucket[h];
+    lds_order();
+    const bool won = open && __builtin_amdgcn_ds_bpermute(4 * lead, key) == key;
+    const bool own = won && lead == lane;
+    const unsigned long long m = __ballot(own);
+    const int r = total + __popcll(m & ((1ull << lane) - 1ull));
+    const int lr = __builtin_amdgcn_ds_bpermute(4 * lead, r);
+    rank = won ? lr : rank;
+    leads = leads || own;
+    total += __popcll(m);
+    open = open && !won;
+    mul = (mul * 0x9E3779B1u + 0x7F4A7C15u) | 1u;
+  } while (__any(open) && total <= most);
+  return total;
+}
+
 // Wave-cooperative staging of edge rows (one lane per ray).  Rays of a
-// coherent tile often stand in the same few cells (6 distinct ones a step on
-// the 100k-site scene, 78% of the steps within 8): when the live lanes of the
-// wave sit in at most kStageCells distinct cells whose rows fit the wave's LDS
-// slab together, the wave copies those rows into the slab, packed, 64 records
-// a load with all loads under way at once, and every live lane reads its row
-// from there; otherwise each lane gathers its own row from global memory.  The
-// choice is per wave and step (mixing both within one step was slower: the two
-// loops then run one after the other), and the exit search sees the same
-// records in the same order either way, less those that cannot be an exit:
-// on the grid schedule, whose waves hold one small screen tile, the faces that
-// point away from every ray of the wave (about half) never reach the slab.
+// coherent tile stand in few distinct cells at a time: 6 a step on the
+// 100k-site scene, 16 on the 4M-site one (28 in one step of ten).  When the
+// live lanes of the wave sit in at most kStageCells cells of at most
+// 64 kStageLoads faces together, the wave reads those rows packed, 64 records
+// a load, and keeps in its LDS slab, in their order, the faces that do not
+// point away from every ray of the wave: about half.  If these fit, every live
+// lane searches its row there; otherwise each lane gathers its own row from
+// global memory.  The choice is per wave and step (mixing both within one step
+// was slower: the two loops then run one after the other), and the exit search
+// decides the same either way: a face left out is no exit of any of the rays.
 //
-// The 100k-site frame is bound by VALU issue (0.74 of it before), 14
-// instructions per face: 577 -> 541 us, two maps 1280x840 922 -> 836 us,
-// spherical harmonics 775 -> 713 us.  Sixteen cells instead of eight: 807 us
-// (registers); loading each texel ahead of the search: 580 us; groups of eight
-// records in flight in the gathered search: 638 us (one wave per SIMD less).
-constexpr int kStageCells = 8;
-constexpr int kStageRecords = 256;
-constexpr int kStageBytesPerWave = kStageRecords * 16;
-constexpr int kStagePad = 64;  // behind the last slab: a search reads three records past its row
+// What bounds the walk: gathers, for scenes beyond the L2 (texture data path
+// busy 0.98 of the 4M-site forward's cycles), and VALU issue, 14 instructions
+// per face, for smaller ones (0.74 of a 100k-site frame's).  Staging serves
+// both.  Rows copied one after the other (a trip to memory each, at most
+// eight): 100k-site frame 577 us, two maps 1280x840 922, spherical harmonics
+// 775, 4M-site forward + backward 58.4 ms, 311k thin-lens rays 465 us; packed
+// and culled, eight cells: 541, 836, 713 us, 58.4 ms, 465 us; up to 32 cells
+// ranked by rank_keys: 539, 829, 658 us, 54.5 ms, 431 us.  Loading each texel
+// ahead of the search (580 us a frame) or eight gathered records at a time
+// (638 us) costs registers and with them a wave per SIMD.
+constexpr int kStageCells = 32;      // a power of two (bisection), two rows of 16 lanes (scan)
+constexpr int kStageRecords = 256;   // in the slab
+constexpr int kStageLoads = 8;       // of 64 records each
+// a wave's slab, the rows' numbers (256 bytes) and its cone of directions (a
+// search reads up to three records past its row: they may be these)
+constexpr int kStageBytesPerWave = kStageRecords * 16 + 256 + 32;
 constexpr int kStageMaxGap = 8;
 
 // The directions of a wave's rays: centre c and a radius with |w - c| <= rho
 // for every ray (wave-uniform).
-struct Cone {
+// Held in the wave's LDS, as registers are short in the walk.
+struct __align__(16) Cone {
   float cx, cy, cz, rho;
 };
 
@@ -417,103 +465,88 @@ __device__ __forceinline__ Cone wave_cone(const RayIn& r, bool has) {
 // Every lane of the wave must call this; alive: the lane's walk goes on, at
 // cell cur with record c.  Returns the lane's staged row and its length, or
 // null when the wave's rows were not staged (then staged = false on every
-// lane).  CULL: faces that no ray of the wave can leave through (m.w < 0 over
-// the whole cone) are left out of the slab.
-template <bool CULL>
+// lane).  Faces that no ray of the wave can leave through (m.w < 0 over the
+// whole cone) are left out of the slab.
 __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ edges, float4* slab,
-                                                    bool alive, int cur, const Cell& c,
-                                                    const Cone& cone, int lane, int& len,
-                                                    bool& staged) {
-  unsigned long long pend = __ballot(alive);
-  int mine = 0;
-  int from[kStageCells], delta[kStageCells];  // first record of each row; its source less that
-  int n = 0, used = 0;
-#pragma unroll
-  for (int q = 0; q < kStageCells; ++q) {
-    if (pend == 0ull) break;
-    const int leader = __ffsll((long long)pend) - 1;  // wave-uniform
-    const int cl = __builtin_amdgcn_readlane(cur, leader);
-    const int deg = __builtin_amdgcn_readlane(c.deg, leader);
-    from[q] = used;
-    delta[q] = __builtin_amdgcn_readlane(c.off, leader) - used;
-    const bool same = alive && cur == cl;
-    pend &= ~__ballot(same);
-    mine = same ? (CULL ? q : used) : mine;  // the row's number, or its start
-    used += deg;
-    n = q + 1;
-  }
-  staged = pend == 0ull && used <= kStageRecords;
-  if (!staged) return nullptr;
-  // the slab's previous rows have been read by every lane (LDS operations of
+                                                    bool alive, int cur, const Cell& c, int lane,
+                                                    int& len, bool& staged) {
+  staged = false;
+  int* info = reinterpret_cast<int*>(slab + kStageRecords);
+  int rank;
+  bool leads;
+  // (the slab's previous rows have been read by every lane: LDS operations of
   // one wave complete in order)
-  __builtin_amdgcn_wave_barrier();
-  // the rows end to end, 64 records a load, every load under way before the
-  // first is used
-  constexpr int kLoads = kStageRecords / 64;
-  float4 v[kLoads];
+  const int n = rank_keys(cur, alive, reinterpret_cast<unsigned char*>(info), lane, kStageCells,
+                          rank, leads);
+  if (n > kStageCells) return nullptr;
+  using i32x2 = int __attribute__((ext_vector_type(2)));
+  i32x2* rows = reinterpret_cast<i32x2*>(info);
+  if (leads) rows[rank] = i32x2{c.off, c.deg};
+  lds_order();
+  // lane m < n: row m, its records at [from, from + deg) of the packed rows
+  i32x2 row = i32x2{0, 0};
+  if (lane < n) row = rows[lane];
+  int sum = row.y;
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x111, 0xF, 0xF, false);  // row_shr:1
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x112, 0xF, 0xF, false);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x114, 0xF, 0xF, false);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x118, 0xF, 0xF, false);
+  const int low = __builtin_amdgcn_readlane(sum, 15);
+  sum += lane >= 16 ? low : 0;
+  const int used = __builtin_amdgcn_readlane(sum, 31);  // (rows past n have none)
+  if (used > 64 * kStageLoads) return nullptr;
+  const int from = sum - row.y;
+  const int delta = row.x - from;
+  const Cone cone = *reinterpret_cast<const Cone*>(info + 64);
+  int start = 0, kept = 0;
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    if (64 * i >= used) break;
-    const int r = 64 * i + lane;
-    int d = delta[0];
+  for (int half = 0; half < kStageLoads; half += 4) {
+    if (64 * half >= used) break;
+    // four loads under way at a time
+    float4 v[4];
 #pragma unroll
-    for (int q = 1; q < kStageCells; ++q) {
-      if (q >= n) break;
-      d = r >= from[q] ? delta[q] : d;
+    for (int i = 0; i < 4; ++i) {
+      if (64 * (half + i) >= used) break;
+      const int r = 64 * (half + i) + lane;
+      int m = 0;  // the last row that starts at or before r
+#pragma unroll
+      for (int step = kStageCells / 2; step >= 1; step >>= 1) {
+        if (step >= n) continue;
+        const int at = __builtin_amdgcn_ds_bpermute(4 * (m + step), from);
+        m = m + step < n && at <= r ? m + step : m;
+      }
+      const int d = __builtin_amdgcn_ds_bpermute(4 * m, delta);
+      v[i] = edges[r < used ? r + d : 0];
     }
-    v[i] = edges[r < used ? r + d : 0];
-  }
-  if constexpr (!CULL) {
-    len = c.deg;
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      if (64 * i >= used) break;
-      slab[64 * i + lane] = v[i];
+    for (int i = 0; i < 4; ++i) {
+      if (64 * (half + i) >= used) break;
+      const float4 E = v[i];
+      const float b = dot3(E.x, E.y, E.z, cone.cx, cone.cy, cone.cz);
+      const float e = fabsf(E.x) + fabsf(E.y) + fabsf(E.z);
+      const bool keep = 64 * (half + i) + lane < used && !(fmaf(e, cone.rho, b) < 0.0f);
+      const unsigned long long mask = __ballot(keep);
+      const int at = kept + __popcll(mask & ((1ull << lane) - 1ull));
+      if (keep && at < kStageRecords) slab[at] = E;
+      const int lo = from - 64 * (half + i);
+      if (lo > 0) start = kept + __popcll(lo >= 64 ? mask : mask & ((1ull << lo) - 1ull));
+      kept += __popcll(mask);
     }
-    __builtin_amdgcn_wave_barrier();
-    return slab + mine;
   }
-  int start[kStageCells];
-#pragma unroll
-  for (int q = 0; q < kStageCells; ++q) start[q] = 0;
-  int kept = 0;
-#pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    if (64 * i >= used) break;
-    const float4 E = v[i];
-    const float b = dot3(E.x, E.y, E.z, cone.cx, cone.cy, cone.cz);
-    const float e = fabsf(E.x) + fabsf(E.y) + fabsf(E.z);
-    const bool keep = 64 * i + lane < used && !(fmaf(e, cone.rho, b) < 0.0f);
-    const unsigned long long m = __ballot(keep);
-    const int at = kept + __popcll(m & ((1ull << lane) - 1ull));
-    if (keep) slab[at] = E;
-#pragma unroll
-    for (int q = 1; q < kStageCells; ++q) {
-      if (q >= n) break;
-      const int lo = from[q] - 64 * i;
-      if (lo > 0) start[q] = kept + (int)__popcll(lo >= 64 ? m : m & ((1ull << lo) - 1ull));
-    }
-    kept += (int)__popcll(m);
-  }
-  // each lane's row: start and length by the row's number
-  int rows = 0;
-#pragma unroll
-  for (int q = 0; q < kStageCells; ++q) {
-    if (q >= n) break;
-    const int end = q + 1 < n ? start[q + 1 < kStageCells ? q + 1 : 0] : kept;
-    const int w = start[q] | ((end - start[q]) << 16);
-    rows = lane == q ? w : rows;
-  }
-  rows = __builtin_amdgcn_ds_bpermute(4 * mine, rows);
-  len = rows >> 16;
-  __builtin_amdgcn_wave_barrier();
-  return slab + (rows & 0xffff);
+  if (kept > kStageRecords) return nullptr;
+  const int next = __builtin_amdgcn_ds_bpermute(4 * lane + 4, start);
+  int span = start | (((lane + 1 < n ? next : kept) - start) << 16);
+  span = __builtin_amdgcn_ds_bpermute(4 * rank, span);
+  len = span >> 16;
+  lds_order();
+  staged = true;
+  return slab + (span & 0xffff);
 }
 
 // walk_forward with one lane per ray and staged rows.  Every lane of the
 // wave must call this (has_ray = false for lanes without a ray); slab: the
 // wave's kStageBytesPerWave of LDS.
-template <int TEX, int APP, bool E16 = false, bool CULL = false>
+template <int TEX, int APP, bool E16 = false>
 __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const WalkParams& w,
                                                       const RayIn& r, bool has_ray, int lane,
                                                       float4* slab, int32_t* rec, int max_record,
@@ -522,8 +555,9 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
   FwdState<APP> st;
   const bool walk = has_ray && fwd_begin<APP>(st, s, r, cnt);
   bool alive = walk;
-  Cone cone{};
-  if constexpr (CULL) cone = wave_cone(r, walk);
+  const Cone cone = wave_cone(r, walk);
+  if (lane == 0) *reinterpret_cast<Cone*>(reinterpret_cast<int*>(slab + kStageRecords) + 64) = cone;
+  lds_order();
   // after a step whose rows could not be staged the wave waits `wait` steps
   // before it tries again, doubling the wait up to kStageMaxGap while it
   // keeps failing (rays that have spread apart seldom meet again soon, and
@@ -537,7 +571,7 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
       Cell c;
       if (alive) c = st.nc;
       bool staged;
-      row = stage_rows<CULL>(s.edges, slab, alive, st.cur, c, cone, lane, len, staged);
+      row = stage_rows(s.edges, slab, alive, st.cur, c, lane, len, staged);
       if (staged) {
         gap = 1;
       } else {
@@ -683,13 +717,6 @@ __device__ __forceinline__ void table_flush(const GradTable& t, const Grads& g, 
   for (int i = threadIdx.x; i < kTableCap; i += blockDim.x) t.keys[i] = -1;
 }
 
-// Orders a wave's own LDS accesses for the compiler (the hardware keeps them in
-// order).
-__device__ __forceinline__ void lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // One wave's LDS area for merging its records: row c < 16 holds term c of
 // every lane, row 16 the lanes' ranks and other words of the merge.
 constexpr int kMergeStride = 68;  // 16-byte rows that start four banks apart
@@ -728,35 +755,10 @@ __device__ __forceinline__ void emit_records(int key, float ds, float px, float 
   }
   const int n = lane & 15;
   const int grp = lane >> 4;
-  // Rank the distinct keys: each lane writes its number to a bucket chosen by
-  // its key and reads back whose stayed; lanes whose key is that lane's have
-  // their leader, the others go on with another hash.  Every round settles at
-  // least one key.
-  int rank = -1, total = 0;
-  bool leads = false;
-  {
-    unsigned char* bucket = reinterpret_cast<unsigned char*>(word);
-    bool open = key >= 0;
-    unsigned mul = 2654435761u;
-    do {
-      const unsigned h = ((unsigned)key * mul) >> 24;
-      int lead = lane;
-      if (open) bucket[h] = (unsigned char)lane;
-      lds_order();
-      if (open) lead = bucket[h];
-      lds_order();
-      const bool won = open && __builtin_amdgcn_ds_bpermute(4 * lead, key) == key;
-      const bool own = won && lead == lane;
-      const unsigned long long m = __ballot(own);
-      const int r = total + __popcll(m & ((1ull << lane) - 1ull));
-      const int lr = __builtin_amdgcn_ds_bpermute(4 * lead, r);
-      rank = won ? lr : rank;
-      leads = leads || own;
-      total += __popcll(m);
-      open = open && !won;
-      mul = mul * 0x9E3779B1u + 0x7F4A7C15u | 1u;
-    } while (__any(open));
-  }
+  int rank;
+  bool leads;
+  const int total =
+      rank_keys(key, key >= 0, reinterpret_cast<unsigned char*>(word), lane, 64, rank, leads);
   for (int base = 0; base < total; base += 16) {
     using f32x4 = float __attribute__((ext_vector_type(4)));
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};

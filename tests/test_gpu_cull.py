@@ -1,4 +1,4 @@
-"""The grid schedule's staged rows leave out the faces that point away from
+"""The staged rows of the forward walk leave out the faces that point away from
 every ray of the wave: narrow, wide and ragged tiles against the walk that
 searches whole rows (two lanes per ray), bit by bit."""
 import numpy as np
@@ -25,15 +25,16 @@ def ds():
                                        (synth.PINHOLE, 3.1), (synth.FISHEYE, 6.2),
                                        (synth.THIN_LENS, 1.0)])
 @pytest.mark.parametrize("size", [(8, 8), (9, 7), (61, 40)])
-def test_culled_rows_give_the_same_walk(ds, model, fov, size):
-    print(f"[gpu-case] cull model={model} fov={fov} size={size}", flush=True)
+@pytest.mark.parametrize("schedule", [voro.SCHEDULE_GRID, voro.SCHEDULE_PERSISTENT])
+def test_culled_rows_give_the_same_walk(ds, model, fov, size, schedule):
+    print(f"[gpu-case] cull model={model} fov={fov} size={size} schedule={schedule}", flush=True)
     cam = synth.Camera(model, *size, synth.look_at((0.1, -0.2, -0.9), (0.2, 0.1, 0.4)), fov, 4.0,
                        lens_radius=0.2, focus_dist=1.0, spp=4 if model == synth.THIN_LENS else 1)
     n = cam.n_rays
     out = []
     for lanes in (1, 2):
         k = torch.zeros(n, dtype=torch.int32, device="cuda")
-        p = voro.default_params(lanes_per_ray=lanes, schedule=voro.SCHEDULE_GRID)
+        p = voro.default_params(lanes_per_ray=lanes, schedule=schedule)
         rgb, T, _ = voro.voro_render_views_fwd(ds, [cam], p, nsteps=k)
         torch.cuda.synchronize()
         out.append([x.cpu().numpy() for x in (rgb, T, k)])
