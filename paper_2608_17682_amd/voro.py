@@ -145,7 +145,7 @@ def _stream(stream=None):
     if stream is not None:
         return ctypes.c_void_p(stream)
     import torch
-    if torch.cuda.is_available():
+    if torch.cuda.is_initialized() or torch.cuda.is_available():
         return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     return ctypes.c_void_p(0)
 
@@ -191,6 +191,9 @@ def camera_of(cam) -> voro_camera:
 
 
 def camera_array(cams: Sequence) -> ctypes.Array:
+    """The cameras as a voro_camera array (as it is, if it is one already)."""
+    if isinstance(cams, ctypes.Array) and cams._type_ is voro_camera:
+        return cams
     arr = (voro_camera * len(cams))()
     for i, c in enumerate(cams):
         arr[i] = c if isinstance(c, voro_camera) else camera_of(c)
@@ -220,7 +223,6 @@ class DeviceScene:
     """
 
     def __init__(self, sites, density, nbr_off, nbr_idx, texels):
-        import torch
         self.sites = sites
         self.density = density
         self.nbr_off = nbr_off
@@ -233,7 +235,19 @@ class DeviceScene:
         self.tex_dtype = _TEX_CODE[str(texels.dtype).replace("torch.", "")]
         self.ws = None
         self.ws_bytes = 0
-        self.stats = torch.zeros(STAT_COUNT, dtype=torch.int64, device=sites.device)
+        self._stats = None
+
+    @property
+    def stats(self):
+        """A zeroed counter array for this scene (made when first asked for)."""
+        if self._stats is None:
+            import torch
+            self._stats = torch.zeros(STAT_COUNT, dtype=torch.int64, device=self.sites.device)
+        return self._stats
+
+    @stats.setter
+    def stats(self, t):
+        self._stats = t
 
     @property
     def n(self):
@@ -381,7 +395,7 @@ def voro_render_bwd(ds: DeviceScene, o, d, tmax, start, rgb, T, g_rgb, g_T=None,
 def voro_gen_rays(cams, device="cuda", stream=None):
     import torch
     arr = camera_array(cams)
-    nr, _ = voro_camera_counts(list(arr))
+    nr, _ = voro_camera_counts(arr)
     o = torch.empty((nr, 3), dtype=torch.float32, device=device)
     d = torch.empty((nr, 3), dtype=torch.float32, device=device)
     tm = torch.empty(nr, dtype=torch.float32, device=device)
@@ -410,7 +424,7 @@ def voro_render_views_fwd(ds: DeviceScene, cams, params=None, rgb=None, T=None, 
     cap exits for voro_render_views_bwd."""
     import torch
     arr = camera_array(cams)
-    nr, npx = voro_camera_counts(list(arr))
+    nr, npx = voro_camera_counts(arr)
     trace, cap = _trace_args(trace, nr)
     dev = ds.sites.device
     rgb = torch.empty((npx, 3), dtype=torch.float32, device=dev) if rgb is None else rgb
@@ -447,7 +461,7 @@ def voro_render_views_bwd(ds: DeviceScene, cams, rgb, T, ray_rgbT, g_rgb, g_T=No
     """trace: None (every exit is searched again) or the forward's stored exits."""
     import torch
     arr = camera_array(cams)
-    nr, _ = voro_camera_counts(list(arr))
+    nr, _ = voro_camera_counts(arr)
     trace, cap = _trace_args(trace, nr)
     dev = ds.sites.device
     if g_sites is None:
