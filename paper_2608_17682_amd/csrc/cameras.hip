@@ -182,18 +182,12 @@ __device__ __forceinline__ void write_ray_out(const ViewsArgs& a, const TileRay&
 // edge rows (dynamic LDS: kStageBytesPerWave per wave), also when gathered
 // rows are ranked in half precision.  The exact one-lane-per-ray walks are
 // held to 96 VGPRs, five waves per SIMD, at the price of spills around the
-// walk loop (100k-site frame 592 us at four waves, 556 at five, 574 at six;
-// 4M-site persistent forward + backward 54.3 ms at five, 56.0 at four);
+// walk loop (kFwdWaves; 100k-site frame 592 us at four waves, 556 at five, 574
+// at six; 4M-site persistent forward + backward 54.3 ms at five, 56.0 at four);
 // spherical harmonics need 128 (at 96: 1029 us instead of 708).
-template <int LPR, int APP, bool PERSIST, bool E16>
-struct FwdWaves {
-  static constexpr int value =
-      LPR > 1 ? 1 : APP == 0 ? (PERSIST && E16 ? 1 : 5) : APP == 1 ? (E16 ? 1 : 5) : 4;
-};
-
 template <int LPR, int TEX, int APP, bool PERSIST, bool E16>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(FwdWaves<LPR, APP, PERSIST, E16>::value, 8)))
+    __attribute__((amdgpu_waves_per_eu(LPR == 1 ? kFwdWaves<APP, E16> : 1, 8)))
     k_views_fwd(ViewsArgs a) {
   extern __shared__ float4 slabs[];
   __shared__ unsigned long long s_stats[kWgStats];

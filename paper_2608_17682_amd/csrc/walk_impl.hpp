@@ -417,10 +417,14 @@ __device__ __forceinline__ int rank_keys(int key, bool open, unsigned char* buck
 // eight): 100k-site frame 577 us, two maps 1280x840 922, spherical harmonics
 // 775, 4M-site forward + backward 58.4 ms, 311k thin-lens rays 465 us; packed
 // and culled, eight cells: 541, 836, 713 us, 58.4 ms, 465 us; up to 32 cells
-// ranked by rank_keys: 539, 829, 658 us, 54.5 ms, 431 us.  Loading each texel
-// ahead of the search (580 us a frame) or eight gathered records at a time
+// ranked by rank_keys: 539, 829, 658 us, 54.5 ms, 431 us, each record's row
+// found by bisection over the lanes; by counting the marks of the rows' starts
+// (one trip to LDS instead of five): 495, 780, 597 us, 54.6 ms, 378 us.  (Ranks
+// counted from the leaders' mask and the next row's start by a lane shift,
+// without their LDS permutes, were slower again: 530, 820, 696 us, 59.4 ms.)
+// Loading each texel ahead of the search (580 us a frame) or eight gathered records at a time
 // (638 us) costs registers and with them a wave per SIMD.
-constexpr int kStageCells = 32;      // a power of two (bisection), two rows of 16 lanes (scan)
+constexpr int kStageCells = 32;      // two rows of 16 lanes (scan)
 constexpr int kStageRecords = 256;   // in the slab
 constexpr int kStageLoads = 8;       // of 64 records each
 // a wave's slab, the rows' numbers (256 bytes) and its cone of directions (a
@@ -497,8 +501,20 @@ __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ e
   if (used > 64 * kStageLoads) return nullptr;
   const int from = sum - row.y;
   const int delta = row.x - from;
+  // a byte per packed record, set where a row starts (a row without faces would
+  // share its start: such cells are left to the gathered search)
+  unsigned char* flag = reinterpret_cast<unsigned char*>(slab);
+  if (__any(lane < n && row.y == 0)) return nullptr;
+  reinterpret_cast<i32x2*>(flag)[lane] = i32x2{0, 0};
+  lds_order();
+  if (lane < n) flag[from] = 1;
+  lds_order();
   const Cone cone = *reinterpret_cast<const Cone*>(info + 64);
-  int start = 0, kept = 0;
+  unsigned char f[kStageLoads];
+#pragma unroll
+  for (int i = 0; i < kStageLoads; ++i) f[i] = flag[64 * i + lane];
+  lds_order();
+  int start = 0, kept = 0, first = -1;
 #pragma unroll
   for (int half = 0; half < kStageLoads; half += 4) {
     if (64 * half >= used) break;
@@ -508,13 +524,10 @@ __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ e
     for (int i = 0; i < 4; ++i) {
       if (64 * (half + i) >= used) break;
       const int r = 64 * (half + i) + lane;
-      int m = 0;  // the last row that starts at or before r
-#pragma unroll
-      for (int step = kStageCells / 2; step >= 1; step >>= 1) {
-        if (step >= n) continue;
-        const int at = __builtin_amdgcn_ds_bpermute(4 * (m + step), from);
-        m = m + step < n && at <= r ? m + step : m;
-      }
+      // the last row that starts at or before r
+      const unsigned long long starts = __ballot(f[half + i] != 0);
+      const int m = first + __popcll(starts & (~0ull >> (63 - lane)));
+      first += __popcll(starts);
       const int d = __builtin_amdgcn_ds_bpermute(4 * m, delta);
       v[i] = edges[r < used ? r + d : 0];
     }
@@ -542,6 +555,10 @@ __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ e
   staged = true;
   return slab + (span & 0xffff);
 }
+
+// Waves per SIMD that a forward kernel with one lane per ray is held to.
+template <int APP, bool E16>
+constexpr int kFwdWaves = APP == 2 ? 4 : E16 ? 4 : 5;
 
 // walk_forward with one lane per ray and staged rows.  Every lane of the
 // wave must call this (has_ray = false for lanes without a ray); slab: the
@@ -647,8 +664,8 @@ __device__ __forceinline__ float* record_addr(const Grads& g, int key, int c, in
 // write together 5.6).  So records are summed across the wave first, exactly
 // (emit_records), the sums are added by plain reads and writes, and entries
 // that later rays cannot reach any more make room for new ones.  4M sites, 8
-// views: device requests 817 M -> 250 M, LDS busy 0.78 -> 0.2, adjoint 51.9 ->
-// 29.2 ms; 100k sites, 800x800: 1.17 -> 0.72 ms (two maps: 2.40 -> 1.50 ms).
+// views: device requests 817 M -> 130 M, LDS busy 0.78 -> 0.25, adjoint 51.9 ->
+// 29.7 ms; 100k sites, 800x800: 1.17 -> 0.72 ms (two maps: 2.40 -> 1.50 ms).
 // Taking over a fixed way per key instead of one that moves on with the steps
 // left finished cells in place: 32.0 ms at 4M sites.  Locking with a loop over
 // single slots instead of one 16-byte read of a set cost 240 us of the 100k
