@@ -57,7 +57,7 @@ struct ViewsArgs {
   WalkParams w;
   CamTable ct;
   const int32_t* center_cell;  // [V] cell of each camera centre
-  unsigned int* counters;      // [kXcd]
+  unsigned int* counters;      // [kXcd], and the ticket at kViewsTicket bytes
   int total_tiles;
   int tile_w, tile_h;
   // refill schedule: strips of strip_tiles tiles inside one view
@@ -89,6 +89,19 @@ __device__ __forceinline__ ExitTrace ray_trace(const ViewsArgs& a, bool has, int
   x.stride = a.n_rays;
   x.cap = a.trace_cap;
   return x;
+}
+
+// Every walk of a multi-view launch puts the ticket that k_views_locate counts
+// with back to zero (that kernel has ended, the next one has not begun): whatever
+// a launch finds there, say after two calls overlapped on one scratch, the next
+// one counts from zero again.  Called at a walk's end: at its start the wave's
+// first loads would wait for the store (0.9 of a 64x64-pixel frame's 35 us); by
+// every thread of a workgroup, as a thread's number would be held across the walk
+// (a register: 800x800 frame with spherical harmonics 596 -> 639 us).
+__device__ __forceinline__ void reset_ticket(const ViewsArgs& a) {
+  if (blockIdx.x == 0)
+    __hip_atomic_store(a.counters + kViewsTicket / sizeof(unsigned), 0u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Next work unit from the XCD-partitioned queue (one thread asks), or -1
@@ -238,6 +251,7 @@ __global__ void __launch_bounds__(256)
     }
     if constexpr (!PERSIST) break;
   }
+  reset_ticket(a);
   if constexpr (PERSIST) {
     __syncthreads();
     if (a.stats) wg_stats_flush(s_stats, a.stats);
@@ -297,6 +311,7 @@ __global__ void __launch_bounds__(256) k_views_fwd_refill(ViewsArgs a) {
       }
     }
   }
+  reset_ticket(a);
   if (a.stats) {
     flush_counters(cnt, true, lane, a.stats);
     const uint32_t cp = wave_sum_u32(capped_n);
@@ -391,6 +406,7 @@ __global__ void __launch_bounds__(256)
     __syncthreads();
     if constexpr (!PERSIST) break;
   }
+  reset_ticket(a);
   if constexpr (PERSIST) {
     __syncthreads();
     if (a.stats) wg_stats_flush(s_stats, a.stats);

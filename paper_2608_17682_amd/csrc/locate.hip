@@ -122,7 +122,8 @@ __global__ void __launch_bounds__(64) k_locate_final(const BestD* __restrict__ p
 // The multi-view launch's start in one kernel: the cells of the camera centres
 // (which travel as kernel arguments), and the tile-queue counters zeroed.
 // Workgroup (chunk, view) leaves its chunk's nearest site in `partial`; the one
-// that takes the last ticket reduces them and puts the ticket back to zero.
+// that takes the last ticket reduces them and puts the ticket back to zero (as
+// the walk behind this kernel does, so that no bad value outlives a call).
 // Stores and loads of the partial results are device-scope atomics, as the
 // workgroups run on XCDs with L2s of their own.  One launch instead of three:
 // 100k-site frames spent 18 us on them, thumbnails of 512 sites 10 of 61 us.
