@@ -169,33 +169,46 @@ __global__ void __launch_bounds__(256) k_permute_rows(const int* __restrict__ pe
                                                       int* __restrict__ off_out,
                                                       int* __restrict__ idx_out) {
   __shared__ int s_dst[kRowCells + 1];
-  __shared__ int s_src[kRowCells];  // -1: a malformed input row, left empty
+  __shared__ int s_src[kRowCells];
+  __shared__ int s_len[kRowCells];  // -1: a malformed input row, left empty
+  __shared__ int s_bad;
   const int t = threadIdx.x;
   const int k0 = blockIdx.x * kRowCells;
   const int nk = min(kRowCells, n - k0);
   if (t <= nk) s_dst[t] = off_out[k0 + t];
+  if (t == 0) s_bad = 0;
+  __syncthreads();
   if (t < nk) {
     const int o = perm[k0 + t];
     const int s = off_in[o];
     const int e = off_in[o + 1];
-    const int dst = off_out[k0 + t];
+    const int dst = s_dst[t];
     // offsets out of order or range
     const bool bad = s < 0 || e < s || e > m || dst < 0 || dst > m - (e - s);
-    s_src[t] = bad ? -1 : s;
+    s_src[t] = s;
+    s_len[t] = bad ? -1 : e - s;
+    if (bad) s_bad = 1;
   }
   __syncthreads();
-  // the output offsets are running sums of lengths >= 0 (the bounds are for
-  // malformed input, whose sums may leave [0, m])
-  const int hi = min(s_dst[nk], m);
-  for (int w = max(s_dst[0], 0) + t; w < hi; w += 256) {
-    int c = 0;  // the last row that starts at or before w
+  if (!s_bad) {
+    // each row starts where the one before it ends, within [0, m]
+    for (int w = s_dst[0] + t; w < s_dst[nk]; w += 256) {
+      int c = 0;  // the last row that starts at or before w
 #pragma unroll
-    for (int step = kRowCells / 2; step >= 1; step >>= 1)
-      if (c + step < nk && s_dst[c + step] <= w) c += step;
-    const int s = s_src[c];
-    if (s < 0) continue;
-    const int j = idx_in[s + (w - s_dst[c])];
-    idx_out[w] = (j >= 0 && j < n) ? inv_perm[j] : j;
+      for (int step = kRowCells / 2; step >= 1; step >>= 1)
+        if (c + step < nk && s_dst[c + step] <= w) c += step;
+      const int j = idx_in[s_src[c] + (w - s_dst[c])];
+      idx_out[w] = (j >= 0 && j < n) ? inv_perm[j] : j;
+    }
+    return;
+  }
+  // a malformed row among them (its length, and with it the sums behind it, may
+  // be anything): row by row, 16 lanes each
+  for (int c = t >> 4; c < nk; c += 16) {
+    for (int i = t & 15; i < s_len[c]; i += 16) {
+      const int j = idx_in[s_src[c] + i];
+      idx_out[s_dst[c] + i] = (j >= 0 && j < n) ? inv_perm[j] : j;
+    }
   }
 }
 
