@@ -191,13 +191,15 @@ __global__ void __launch_bounds__(256) k_permute_rows(const int* __restrict__ pe
   }
   __syncthreads();
   if (!s_bad) {
-    // each row starts where the one before it ends, within [0, m]
-    for (int w = s_dst[0] + t; w < s_dst[nk]; w += 256) {
+    // each row starts where the one before it ends, within [0, m] (unsigned: a
+    // turn past m can lie above 2^31)
+    const unsigned hi = (unsigned)s_dst[nk];
+    for (unsigned w = (unsigned)s_dst[0] + t; w < hi; w += 256u) {
       int c = 0;  // the last row that starts at or before w
 #pragma unroll
       for (int step = kRowCells / 2; step >= 1; step >>= 1)
-        if (c + step < nk && s_dst[c + step] <= w) c += step;
-      const int j = idx_in[s_src[c] + (w - s_dst[c])];
+        if (c + step < nk && (unsigned)s_dst[c + step] <= w) c += step;
+      const int j = idx_in[(unsigned)s_src[c] + (w - (unsigned)s_dst[c])];
       idx_out[w] = (j >= 0 && j < n) ? inv_perm[j] : j;
     }
     return;

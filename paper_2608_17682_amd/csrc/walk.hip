@@ -103,13 +103,15 @@ __global__ void __launch_bounds__(256) k_prepare(PrepArgs a) {
   }
   __syncthreads();
   if (!s_bad) {
-    // the offsets ascend from 0 or more to m or less
-    for (int e = s_off[0] + t; e < s_off[nc]; e += 256) {
+    // the offsets ascend from 0 or more to m or less (unsigned: a turn past m
+    // can lie above 2^31)
+    const unsigned hi = (unsigned)s_off[nc];
+    for (unsigned e = (unsigned)s_off[0] + t; e < hi; e += 256u) {
       int c = 0;  // the last cell whose row starts at or before e
 #pragma unroll
       for (int step = kPrepCells / 2; step >= 1; step >>= 1)
-        if (c + step < nc && s_off[c + step] <= e) c += step;
-      prepare_edge(a, c0 + c, e, s_p[c][0], s_p[c][1], s_p[c][2]);
+        if (c + step < nc && (unsigned)s_off[c + step] <= e) c += step;
+      prepare_edge(a, c0 + c, (int)e, s_p[c][0], s_p[c][1], s_p[c][2]);
     }
     return;
   }
@@ -117,8 +119,8 @@ __global__ void __launch_bounds__(256) k_prepare(PrepArgs a) {
   for (int c = t >> 4; c < nc; c += 16) {
     const int off = s_off[c], end = s_off[c + 1];
     if (off < 0 || end < off || end > a.m) continue;
-    for (int e = off + (t & 15); e < end; e += 16)
-      prepare_edge(a, c0 + c, e, s_p[c][0], s_p[c][1], s_p[c][2]);
+    for (int e = t & 15; e < end - off; e += 16)
+      prepare_edge(a, c0 + c, off + e, s_p[c][0], s_p[c][1], s_p[c][2]);
   }
 }
 
