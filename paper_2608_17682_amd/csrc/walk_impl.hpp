@@ -485,7 +485,9 @@ __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ e
   if (n > kStageCells) return nullptr;
   using i32x2 = int __attribute__((ext_vector_type(2)));
   i32x2* rows = reinterpret_cast<i32x2*>(info);
-  if (leads) rows[rank] = i32x2{c.off, c.deg};
+  // (no longer than what cannot be staged anyway, so that the sum of 32 lengths
+  // stays an int: rows of a malformed adjacency can overlap)
+  if (leads) rows[rank] = i32x2{c.off, min(c.deg, 64 * kStageLoads + 1)};
   lds_order();
   // lane m < n: row m, its records at [from, from + deg) of the packed rows
   i32x2 row = i32x2{0, 0};

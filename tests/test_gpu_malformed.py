@@ -55,3 +55,32 @@ def test_sound_rows_are_reordered(dev, name, off, before, after):
             sound += e - s
         at = i32(at + max(0, i32(e - s)))
     assert sound >= 10
+
+
+def test_overlapping_rows_longer_than_an_int_together(dev):
+    # 32 cells of one position whose rows are all the same 2^26 ids (between them
+    # rows that end before they start): a wave that stands in all of them cannot
+    # stage 2^31 faces.  The one real face, of the first id, is at x = 0.5; the
+    # cell behind it has no row, so each ray ends there, at its extent.
+    m, n = 2 ** 26, 64
+    print(f"[gpu-case] malformed: 32 rows of {m} ids", flush=True)
+    idx = torch.full((m,), -1, dtype=torch.int32, device=dev)
+    idx[0] = 1
+    sites = torch.zeros((n, 3), device=dev)
+    sites[1, 0] = 1.0
+    off = torch.tensor([0, m] * (n // 2) + [0], dtype=torch.int32, device=dev)
+    ds = voro.DeviceScene(sites, torch.full((n,), 0.5, device=dev), off, idx,
+                          torch.ones((n, 2, 2, 4), device=dev))
+    voro.voro_prepare(ds)
+    R = n // 2
+    o = torch.zeros((R, 3), device=dev)
+    d = torch.zeros((R, 3), device=dev)
+    d[:, 0] = 1.0
+    start = torch.arange(0, n, 2, dtype=torch.int32, device=dev)
+    k = torch.zeros(R, dtype=torch.int32, device=dev)
+    rgb, T = voro.voro_render_fwd(ds, o, d, torch.full((R,), 2.0, device=dev), start,
+                                  voro.default_params(lanes_per_ray=1), nsteps=k)
+    assert k.tolist() == [2] * R
+    # exp(-0.5 * 2) in two FP32 factors
+    np.testing.assert_allclose(T.cpu().numpy(), np.exp(-1.0), rtol=1e-6)
+    np.testing.assert_allclose(rgb.cpu().numpy(), 1.0 - np.exp(-1.0), rtol=1e-6)
