@@ -194,10 +194,10 @@ __device__ __forceinline__ ExitTrace ray_exits(const RayArgs& a, int ray) {
 
 // One lane per ray walks with staged edge rows (dynamic LDS:
 // kStageBytesPerWave per wave), also when gathered rows are ranked in half
-// precision, at the occupancy of the multi-view forward.
-template <int LPR, int TEX, int APP, bool E16>
+// precision.  WAVES: the waves per SIMD it is held to.
+template <int LPR, int TEX, int APP, bool E16, int WAVES>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(LPR == 1 ? kFwdWaves<APP, E16> : 1, 8)))
+    __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     k_render_fwd(RayArgs a) {
   extern __shared__ float4 slabs[];
   const int nwaves = blockDim.x >> 6;
@@ -304,6 +304,16 @@ __global__ void __launch_bounds__(256)
   if (a.stats) flush_counters(cnt, sub == 0, lane, a.stats);
 }
 
+// Rays up to which four waves on each of the 1,024 SIMDs hold a launch of one
+// lane per ray.  The fifth wave takes registers, whose spills slow a walk that
+// gathers its rows (scattered rays), so launches that cannot use it do without:
+// 262,144 scattered rays of a 4,000-site scene 281 us with five, 268 with four,
+// of 300k sites 478 and 461; lens rays of 100k sites 288 and 280.  Larger ones
+// gain more where their rays share cells than they lose where not: 1,280,000
+// lens rays 846 us with five, 922 with four; a million scattered ones 3,540 and
+// 3,320.
+constexpr int kFiveWaveRays = 1024 * 4 * 64;
+
 template <int LPR, int TEX, int APP>
 static void launch_ray_kernel(bool backward, const RayArgs& a, int blocks, int block,
                               hipStream_t st) {
@@ -311,12 +321,18 @@ static void launch_ray_kernel(bool backward, const RayArgs& a, int blocks, int b
     const size_t lds = LPR == 1 ? (size_t)(block / 64) * kStageBytesPerWave : 0;
     if constexpr (LPR == 1) {
       if (a.w.edge16) {
-        hipLaunchKernelGGL((k_render_fwd<1, TEX, APP, true>), dim3(blocks), dim3(block), lds, st,
-                           a);
+        hipLaunchKernelGGL((k_render_fwd<1, TEX, APP, true, kFwdWaves<APP, true>>), dim3(blocks),
+                           dim3(block), lds, st, a);
+        return;
+      }
+      if (a.map.n_rays > kFiveWaveRays) {
+        hipLaunchKernelGGL((k_render_fwd<1, TEX, APP, false, kFwdWaves<APP, false>>),
+                           dim3(blocks), dim3(block), lds, st, a);
         return;
       }
     }
-    hipLaunchKernelGGL((k_render_fwd<LPR, TEX, APP, false>), dim3(blocks), dim3(block), lds, st, a);
+    hipLaunchKernelGGL((k_render_fwd<LPR, TEX, APP, false, LPR == 1 ? 4 : 1>), dim3(blocks),
+                       dim3(block), lds, st, a);
     return;
   }
   if constexpr (APP != 2) {
