@@ -142,7 +142,7 @@ def render_views(sites, density, texels, nbr_off, nbr_idx, cams, params_fwd=None
     stored_exits > 0: the forward keeps each ray's first stored_exits exits
     (8 bytes per ray and step, until the backward) and the adjoint reads them
     instead of searching those steps again."""
-    cams = voro.camera_array(list(cams))
+    cams = voro.camera_array(cams)
     params_fwd = params_fwd or voro.default_params()
     params_bwd = backward_params(params_fwd, params_bwd)
     wants = _wants_grad(sites, density, texels)

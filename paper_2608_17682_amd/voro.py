@@ -191,17 +191,22 @@ def camera_of(cam) -> voro_camera:
 
 
 def camera_array(cams: Sequence) -> ctypes.Array:
-    """The cameras as a voro_camera array (as it is, if it is one already)."""
-    if isinstance(cams, ctypes.Array) and cams._type_ is voro_camera:
-        return cams
+    """A voro_camera array of its own with the cameras."""
     arr = (voro_camera * len(cams))()
     for i, c in enumerate(cams):
         arr[i] = c if isinstance(c, voro_camera) else camera_of(c)
     return arr
 
 
+def _cameras(cams: Sequence) -> ctypes.Array:
+    """The cameras for one call: a voro_camera array goes through as it is."""
+    if isinstance(cams, ctypes.Array) and cams._type_ is voro_camera:
+        return cams
+    return camera_array(cams)
+
+
 def voro_camera_counts(cams) -> tuple:
-    arr = camera_array(cams)
+    arr = _cameras(cams)
     nr, npx = ctypes.c_int64(), ctypes.c_int64()
     _check(lib().voro_camera_counts(arr, len(arr), ctypes.byref(nr), ctypes.byref(npx)),
            "voro_camera_counts")
@@ -394,7 +399,7 @@ def voro_render_bwd(ds: DeviceScene, o, d, tmax, start, rgb, T, g_rgb, g_T=None,
 
 def voro_gen_rays(cams, device="cuda", stream=None):
     import torch
-    arr = camera_array(cams)
+    arr = _cameras(cams)
     nr, _ = voro_camera_counts(arr)
     o = torch.empty((nr, 3), dtype=torch.float32, device=device)
     d = torch.empty((nr, 3), dtype=torch.float32, device=device)
@@ -423,7 +428,7 @@ def voro_render_views_fwd(ds: DeviceScene, cams, params=None, rgb=None, T=None, 
     """trace: None, or int32 [cap, n_rays, 2] that receives each ray's first
     cap exits for voro_render_views_bwd."""
     import torch
-    arr = camera_array(cams)
+    arr = _cameras(cams)
     nr, npx = voro_camera_counts(arr)
     trace, cap = _trace_args(trace, nr)
     dev = ds.sites.device
@@ -445,7 +450,7 @@ def voro_render_views_fwd_noalloc(ds: DeviceScene, cams, params, rgb, T, ray_rgb
                                   nsteps=None, stats=None, stream=None):
     """voro_render_views_fwd with the library's static scratch: every output is
     caller-provided and nothing is allocated (the prepared workspace is read)."""
-    arr = camera_array(cams)
+    arr = _cameras(cams)
     sc = ds.c()
     _check(lib().voro_render_views_fwd_noalloc(ctypes.byref(sc), _ptr(ds.ws), ds.ws_bytes, arr,
                                                len(arr), ctypes.byref(params), _ptr(rgb), _ptr(T),
@@ -460,7 +465,7 @@ def voro_render_views_bwd(ds: DeviceScene, cams, rgb, T, ray_rgbT, g_rgb, g_T=No
                           trace=None):
     """trace: None (every exit is searched again) or the forward's stored exits."""
     import torch
-    arr = camera_array(cams)
+    arr = _cameras(cams)
     nr, _ = voro_camera_counts(arr)
     trace, cap = _trace_args(trace, nr)
     dev = ds.sites.device
