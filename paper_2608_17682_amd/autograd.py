@@ -25,7 +25,7 @@ class VoroRender(torch.autograd.Function):
     def forward(ctx, sites, density, texels, nbr_off, nbr_idx, o, d, tmax, start, params,
                 with_dist, stored_exits):
         ds = voro.DeviceScene(sites.detach().contiguous(), density.detach().contiguous(),
-                              nbr_off, nbr_idx, texels.detach().contiguous())
+                              nbr_off, nbr_idx, texels.detach().contiguous(), counters=False)
         voro.voro_prepare(ds)
         dist = (torch.empty((o.shape[0], 3), dtype=torch.float32, device=o.device)
                 if with_dist else None)
@@ -68,7 +68,7 @@ class VoroRenderViews(torch.autograd.Function):
     def forward(ctx, sites, density, texels, nbr_off, nbr_idx, cams, params_fwd, params_bwd,
                 stored_exits):
         ds = voro.DeviceScene(sites.detach().contiguous(), density.detach().contiguous(),
-                              nbr_off, nbr_idx, texels.detach().contiguous())
+                              nbr_off, nbr_idx, texels.detach().contiguous(), counters=False)
         voro.voro_prepare(ds)
         trace = None
         if stored_exits > 0:

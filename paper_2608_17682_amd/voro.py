@@ -224,10 +224,13 @@ class DeviceScene:
     sites [N,3] f32, density [N] f32, nbr_off [N+1] i32, nbr_idx [M] i32,
     texels [N,R,R,4] f32/f16/bf16 - all contiguous device tensors; texels
     [N,2,R,R,4] hold the surface and view maps of the full appearance model
-    (params.appearance = 1).
+    (params.appearance = 1).  ``stats``: zeroed counters that a caller can pass
+    to the entry points (None with counters=False, for a scene that stays
+    inside a call: one launch less).
     """
 
-    def __init__(self, sites, density, nbr_off, nbr_idx, texels):
+    def __init__(self, sites, density, nbr_off, nbr_idx, texels, *, counters=True):
+        import torch
         self.sites = sites
         self.density = density
         self.nbr_off = nbr_off
@@ -240,19 +243,8 @@ class DeviceScene:
         self.tex_dtype = _TEX_CODE[str(texels.dtype).replace("torch.", "")]
         self.ws = None
         self.ws_bytes = 0
-        self._stats = None
-
-    @property
-    def stats(self):
-        """A zeroed counter array for this scene (made when first asked for)."""
-        if self._stats is None:
-            import torch
-            self._stats = torch.zeros(STAT_COUNT, dtype=torch.int64, device=self.sites.device)
-        return self._stats
-
-    @stats.setter
-    def stats(self, t):
-        self._stats = t
+        self.stats = (torch.zeros(STAT_COUNT, dtype=torch.int64, device=sites.device)
+                      if counters else None)
 
     @property
     def n(self):
@@ -304,7 +296,7 @@ class DeviceScene:
         d = dict(sites=self.sites, density=self.density, nbr_off=self.nbr_off,
                  nbr_idx=self.nbr_idx, texels=self.texels)
         d.update(kw)
-        out = DeviceScene(**d)
+        out = DeviceScene(**d, counters=False)
         out.ws, out.ws_bytes, out.stats = self.ws, self.ws_bytes, self.stats
         return out
 
