@@ -14,7 +14,9 @@ type and the set of camera models in the launch.  Results live in
 ``autotune_table.json`` next to this file.  ``lookup`` returns the tuned
 fields for the exact class, or else for the tuned class with the same
 texture, texel type, camera set and direction and the nearest scene size,
-or else None (the library's defaults then apply).
+or else None (the library's defaults then apply).  ``params_for`` leaves a
+small launch, which those defaults spread over the GPU, to them unless the
+class was tuned on one.
 
     python -m paper_2608_17682_amd.autotune shell100k [config3] [config5]
 """
@@ -100,18 +102,22 @@ def lookup(ds, cams, direction: str) -> Optional[dict]:
     return lookup_key(key_of(ds, cams, direction))
 
 
-# rays up to which a launch leaves its shape to the library, which then splits
-# each ray over several lanes to fill the GPU (the table is tuned on launches
-# of a million rays and more)
+# rays up to which the library's defaults split each ray over several lanes to
+# fill the GPU; a shape tuned on more rays than that leaves it idle
 SMALL_LAUNCH = {"fwd": 1 << 17, "bwd": 1 << 16}
 
 
 def params_for(ds, cams, direction: str):
-    """voro_params with the library defaults and the tuned launch shape (if any)."""
+    """voro_params with the library defaults and the tuned launch shape (if any);
+    a launch of SMALL_LAUNCH rays or fewer takes its shape only from entries that
+    were tuned on such launches (or do not say on how many rays)."""
     from . import voro
     p = voro.default_params()
-    rays = sum(int(c.width) * int(c.height) * int(c.spp) for c in cams)
-    t = lookup(ds, cams, direction) if rays > SMALL_LAUNCH[direction] else None
+    table = _load()
+    small = SMALL_LAUNCH.get(direction, 0)
+    if sum(int(c.width) * int(c.height) * int(c.spp) for c in cams) <= small:
+        table = {k: e for k, e in table.items() if e.get("rays", 0) <= small}
+    t = lookup_key(key_of(ds, cams, direction), table)
     if t:
         for k, v in t.items():
             setattr(p, k, v)
