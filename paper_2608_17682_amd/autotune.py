@@ -113,6 +113,7 @@ def params_for(ds, cams, direction: str):
     were tuned on such launches (or do not say on how many rays)."""
     from . import voro
     p = voro.default_params()
+    cams = list(cams)
     table = _load()
     small = SMALL_LAUNCH.get(direction, 0)
     if sum(int(c.width) * int(c.height) * int(c.spp) for c in cams) <= small:

@@ -43,3 +43,11 @@ def test_small_launches_take_entries_tuned_on_small_launches(table, direction, m
     # the nearest scene among those that count
     table(**{f"n100000_{direction}": LARGE, f"n400000_{direction}": SMALL})
     assert shape(most, direction) == (4, 4, 4) and shape(most + 1, direction) == (1, 16, 4)
+
+
+def test_cameras_of_any_iterable(table):
+    table(n100000_fwd=LARGE)
+    cam = synth.Camera(synth.PINHOLE, 1000, 1000, synth.look_at((0, 0, -3), (0, 0, 0)), 1.0, 6.0)
+    for cams in ([cam], (c for c in [cam]), iter((cam,))):
+        p = autotune.params_for(DS, cams, "fwd")
+        assert (p.lanes_per_ray, p.tile_w, p.tile_h) == (1, 16, 4)
