@@ -46,7 +46,7 @@ def candidates() -> List[dict]:
         while w <= rays:
             h = rays // w
             if max(w, h) <= 8 * min(w, h):
-                for block in (128, 256):
+                for block in (64, 128, 256):
                     for schedule in ((1, 2, 3) if lpr == 1 else (1, 2)):
                         out.append({"lanes_per_ray": lpr, "tile_w": w, "tile_h": h,
                                     "block": block, "schedule": schedule})

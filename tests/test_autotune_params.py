@@ -51,3 +51,12 @@ def test_cameras_of_any_iterable(table):
     for cams in ([cam], (c for c in [cam]), iter((cam,))):
         p = autotune.params_for(DS, cams, "fwd")
         assert (p.lanes_per_ray, p.tile_w, p.tile_h) == (1, 16, 4)
+
+
+def test_committed_entries_come_from_the_tuner():
+    tried = {"fwd": autotune.candidates(),
+             "bwd": [c for c in autotune.candidates() if c["schedule"] != voro.SCHEDULE_REFILL]}
+    for key, e in autotune._load().items():
+        shapes = tried[key.split("|")[-1]]
+        assert {k: e[k] for k in autotune.LAUNCH_FIELDS} in shapes, key
+        assert e["candidates"] == len(shapes), key
