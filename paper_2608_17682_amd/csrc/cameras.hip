@@ -200,7 +200,7 @@ __device__ __forceinline__ void write_ray_out(const ViewsArgs& a, const TileRay&
 // spherical harmonics need 128 (at 96: 1029 us instead of 708).
 template <int LPR, int TEX, int APP, bool PERSIST, bool E16>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(LPR == 1 ? kFwdWaves<APP, E16> : 1, 8)))
+    __attribute__((amdgpu_waves_per_eu(LPR == 1 ? kFwdWaves<APP, E16, PERSIST> : 1, 8)))
     k_views_fwd(ViewsArgs a) {
   extern __shared__ float4 slabs[];
   __shared__ unsigned long long s_stats[kWgStats];

@@ -558,9 +558,13 @@ __device__ __forceinline__ const float4* stage_rows(const float4* __restrict__ e
   return slab + (span & 0xffff);
 }
 
-// Waves per SIMD that a forward kernel with one lane per ray is held to.
-template <int APP, bool E16>
-constexpr int kFwdWaves = APP == 2 ? 4 : E16 ? 4 : 5;
+// Waves per SIMD that a forward kernel with one lane per ray is held to.  The
+// persistent kernels of the larger models, which hold their queue's state as
+// well, are faster without spills (800x800 frame, two maps: 100k sites 884 us at
+// five waves, 764 at three, 4,000 sites 682 and 491; spherical harmonics 845 at
+// four, 736 at three, and 582 and 481).
+template <int APP, bool E16, bool PERSIST = false>
+constexpr int kFwdWaves = PERSIST && APP ? 3 : APP == 2 ? 4 : E16 ? 4 : 5;
 
 // walk_forward with one lane per ray and staged rows.  Every lane of the
 // wave must call this (has_ray = false for lanes without a ray); slab: the
