@@ -157,8 +157,9 @@ typedef struct voro_scene {
  *               vectors"): neighbours are ranked from half-precision copies
  *               of the packed edge vectors (two per 16-byte load) and the
  *               winner's crossing is taken from its full-precision record;
- *               one lane per ray only.  A ray may take a different exit
- *               where two faces are within half-precision error.         [0]
+ *               where the ranking's bounds leave more than one face, the row
+ *               is searched in full precision, so the walk is the exact one;
+ *               one lane per ray only                                    [0]
  *   schedule    multi-view launches: VORO_SCHEDULE_GRID (one work tile per
  *               wave, hardware dispatch), VORO_SCHEDULE_PERSISTENT (waves
  *               loop over an XCD-partitioned tile queue) or

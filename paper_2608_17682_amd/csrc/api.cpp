@@ -133,13 +133,17 @@ voro_status check_appearance(const voro_scene* s, const voro_params* p) {
 
 // Lanes per ray where the caller leaves them open.  One lane per ray needs
 // kFillFwd rays to keep the chip's 1024 SIMDs at four waves; with fewer, each
-// ray's neighbour tests are split over as many lanes as fill it (measured on
-// one MI355X, 100k sites, forward: 4,096 rays 230 us with one lane, 97 with
-// 16; 32,400 rays 244 with one, 120 with eight; 131,071 rays 450 with one, 381
-// with two; 262,144 rays 332 with one, 360 with two).  The adjoint, which
-// splits only its searches, gains up to kFillBwd (4,096 rays 403 with one, 184
-// with 16; 65,536 rays 268 with one, 253 with two; 129,600 rays 301 with one,
-// 380 with two).  A tile size or a variant with one lane only keeps one.
+// ray's neighbour tests are split over as many lanes as fill it.  One MI355X,
+// forward, us with one lane and with the lanes chosen:
+//   rays                  4,096     32,400    131,072   184,900 (two lanes)
+//   frame, 100k sites   259 / 94  253 / 116  253 / 210  256 / 293
+//   scattered rays      368 / 127 364 / 159  453 / 379  618 / 659
+// so the line lies at half of kFillFwd for either kind (262,144 scattered rays:
+// 874 with one lane and 768 with two on 100k sites, 462 and 498 on 300k).  The
+// adjoint, which splits only its searches, gains up to kFillBwd / 2 rays: 4,096
+// rays of a frame 580 / 254 us, 65,536 419 / 377, with stored exits 395 / 182 and
+// 261 / 247; 131,072 488 against 559 with two lanes.
+// A tile size or a variant with one lane only keeps one.
 static int default_lanes(const voro_params* p, int64_t rays, bool backward) {
   constexpr int64_t kFillFwd = 1 << 18, kFillBwd = 1 << 17;
   if (p->tile_w > 0 || p->edge_fp16 || p->schedule == VORO_SCHEDULE_REFILL) return 1;

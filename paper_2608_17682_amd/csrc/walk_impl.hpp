@@ -584,7 +584,8 @@ __device__ __forceinline__ RayOut walk_forward_staged(const DevScene& s, const W
   // after a step whose rows could not be staged the wave waits `wait` steps
   // before it tries again, doubling the wait up to kStageMaxGap while it
   // keeps failing (rays that have spread apart seldom meet again soon, and
-  // each failed try costs a full pass over kStageCells ballots)
+  // each failed try costs a ranking, up to the round that finds more than
+  // kStageCells cells, and the loads of rows whose faces turn out too many)
   int wait = 0, gap = 1;
   while (__any(alive)) {
     const float4* row = nullptr;
@@ -667,8 +668,8 @@ __device__ __forceinline__ float* record_addr(const Grads& g, int key, int c, in
 // What bounds the adjoint: device float atomics leave a CU at most 64 bytes at
 // a time and the chip at 20 G requests/s, wherever the line is held, and LDS
 // float atomics take 3 cycles per active lane (193 per full wave; a read and a
-// write together 5.6).  So records are summed across the wave first, exactly
-// (emit_records), the sums are added by plain reads and writes, and entries
+// write together 5.6).  So records are summed across the wave first, by
+// exact key and in FP32 (emit_records), the sums are added by plain reads and writes, and entries
 // that later rays cannot reach any more make room for new ones.  4M sites, 8
 // views: device requests 817 M -> 130 M, LDS busy 0.78 -> 0.25, adjoint 51.9 ->
 // 29.7 ms; 100k sites, 800x800: 1.17 -> 0.72 ms (two maps: 2.40 -> 1.50 ms).
