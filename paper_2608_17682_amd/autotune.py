@@ -22,6 +22,7 @@ class was tuned on one.
 """
 from __future__ import annotations
 
+import functools
 import json
 import math
 import os
@@ -74,10 +75,17 @@ def key_of(ds, cams, direction: str) -> str:
     return workload_key(ds.n, ds.tex_res, ds.tex_dtype, _models(cams), direction)
 
 
+@functools.lru_cache(maxsize=4)
+def _parsed(text: str) -> Dict[str, dict]:
+    return json.loads(text)
+
+
 def _load() -> Dict[str, dict]:
+    """The table as the file has it now (its text is read each time, and parsed
+    when it is another)."""
     if os.path.exists(TABLE):
         with open(TABLE) as f:
-            return json.load(f)
+            return dict(_parsed(f.read()))
     return {}
 
 

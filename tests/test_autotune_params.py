@@ -60,3 +60,12 @@ def test_committed_entries_come_from_the_tuner():
         shapes = tried[key.split("|")[-1]]
         assert {k: e[k] for k in autotune.LAUNCH_FIELDS} in shapes, key
         assert e["candidates"] == len(shapes), key
+
+
+def test_table_is_the_files_present_text(table):
+    table(n100000_fwd=LARGE)
+    assert shape(1 << 18, "fwd") == (1, 16, 4)
+    autotune._load().clear()           # a caller's copy
+    assert shape(1 << 18, "fwd") == (1, 16, 4)
+    table(n100000_fwd=dict(LARGE, tile_w=32, tile_h=2))     # as long a text
+    assert shape(1 << 18, "fwd") == (1, 32, 2)
