@@ -406,8 +406,8 @@ voro_status voro_render_views_bwd(const voro_scene* scene, void* ws, size_t ws_b
 /*
  * For callers that cannot allocate (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): voro_render_views_fwd
- * with its scratch - the tile-queue counters, the camera centres and their
- * cells, the nearest-site search's partial results - in a static device
+ * with its scratch - the tile-queue counters, the cells of the camera
+ * centres, the nearest-site search's partial results - in a static device
  * array of the library (about 65 KB per GPU, held until the process ends)
  * instead of the workspace.  The workspace is only read: it must hold the
  * records voro_prepare wrote (voro_workspace_size bytes always suffice).
