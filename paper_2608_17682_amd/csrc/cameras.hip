@@ -580,7 +580,7 @@ static_assert(kViewsTicket >= kXcd * 4 && kViewsScratchCenters >= kViewsTicket +
               kViewsScratchPartials - kViewsScratchCenters >= VORO_MAX_VIEWS * 4,
               "views scratch layout");
 
-// Where a launch keeps its scratch: counters, centres and their cells at
+// Where a launch keeps its scratch: the counters and the centres' cells at
 // `base` (kViewsScratchPartials bytes), the partial results at `partials`.
 struct ViewsScratch {
   char* base;

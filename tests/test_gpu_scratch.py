@@ -67,3 +67,49 @@ def test_ticket_left_over_spoils_one_call_at_most(dev, scene, left, spoiled):
         got = voro.voro_render_views_fwd(ds, [second], voro.default_params(schedule=schedule))[0]
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
         assert int(ticket(ds)) == 0
+
+
+# one view takes one kernel for the centres' cells, sixteen of 20,000 sites two
+@pytest.mark.parametrize("views", [1, 16])
+@pytest.mark.parametrize("schedule", ["grid", "persistent"])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_captured_launches_replay_among_eager_ones(dev, views, schedule, noalloc):
+    print(f"[gpu-case] captured views={views} {schedule} noalloc={noalloc}", flush=True)
+    ds = prepared(synth.scene_uniform(20_000, 2, seed=62), dev)
+    rng = np.random.default_rng(views)
+    eyes = rng.uniform(-0.9, 0.9, (2, views, 3))
+    cams, others = ([camera(e) for e in group] for group in eyes)
+    p = voro.default_params(schedule=SCHEDULES[schedule])
+    n = 40 * 24 * views
+    g = torch.randn((n, 3), device=dev)
+    call = voro.voro_render_views_fwd_noalloc if noalloc else voro.voro_render_views_fwd
+
+    def step(rgb, T, grads):
+        call(ds, cams, p, rgb, T)
+        for x in grads:
+            x.zero_()
+        voro.voro_render_views_bwd(ds, cams, rgb, T, None, g, None, p, *grads)
+
+    def buffers():
+        return (torch.empty((n, 3), device=dev), torch.empty(n, device=dev),
+                [torch.empty(s, device=dev) for s in ((ds.n, 3), (ds.n,), tuple(ds.texels.shape))])
+
+    want, got = buffers(), buffers()
+    step(*want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(*got)
+    for replay in range(3):
+        got[0].fill_(-1.0)
+        got[1].fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        for a, b in zip(got[2], want[2]):
+            # the same terms summed in another order
+            np.testing.assert_allclose(a.cpu().numpy(), b.cpu().numpy(), rtol=0,
+                                       atol=1e-5 * float(b.abs().max()))
+        # eager work on the same scratch in between
+        voro.voro_render_views_fwd(ds, others[: 1 + replay], p)
+        assert int(ticket(ds)) == 0
